@@ -80,7 +80,7 @@ struct PrepArgs {
   int d;
 };
 
-// The two gradient kernels. The query-side pass (dq) walks each query frame's kept
+// The gradient passes. The query-side pass (dq) walks each query frame's kept
 // key frames with the forward's work list; the key-side pass (dk, dv) walks each
 // key frame's keeping query frames with the work list of the transposed mask.
 // Items are 5 int32 as in FwdArgs; split frames write fp32 partials [n_slots][B][T][d]
@@ -112,23 +112,28 @@ struct BwdArgs {
   uint32_t keep;     // 0 zeroes that operand (scale 0), else ~0
   uint32_t n_wg_q;   // B * n_items_q * ceil(max(T, P) / bwd_queries_per_workgroup(d))
   uint32_t n_wg_k;   // B * n_items_k * ceil(max(T, P) / bwd_keys_per_workgroup(d))
+  int slots_per_xcd;  // workgroups of the gradient kernels resident per XCD
 };
 
-// Adds the partials of split segments: heavy holds {head, segment, first slot, slots}.
-struct SumArgs {
+// Adds the partials of split segments, of up to three gradients in one launch: heavy holds
+// {head, segment, first slot, slots}.
+struct SumJob {
   const float* ws;
   const int32_t* heavy;
   int n_heavy;
+  uint16_t* out;
+};
+struct SumArgs {
+  SumJob job[3];
+  int n_jobs;  // >= 1
   int B, H, F, T, d;
   int P;
-  uint16_t* out;
 };
 
 int bwd_queries_per_workgroup(int d);
 int bwd_keys_per_workgroup(int d);
 hipError_t launch_bwd_prep(const PrepArgs& a, hipStream_t stream);
-hipError_t launch_bwd_dq(const BwdArgs& a, hipStream_t stream);
-hipError_t launch_bwd_dkdv(const BwdArgs& a, hipStream_t stream);
+hipError_t launch_bwd(const BwdArgs& a, hipStream_t stream);
 hipError_t launch_sum_partials(const SumArgs& a, hipStream_t stream);
 
 }  // namespace ta

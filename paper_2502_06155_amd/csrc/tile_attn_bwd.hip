@@ -49,6 +49,7 @@
 
 #include "launch.h"
 #include "tile_common.h"
+#include "unit_order.h"
 
 namespace ta {
 namespace {
@@ -73,6 +74,10 @@ constexpr int kRowsPerWg = kBwdWaves * 32;
 enum KeyPass { kDkDv = 0, kDvOnly = 1, kDkOnly = 2 };
 template <int D>
 constexpr bool split_key_pass() { return D == 128; }
+
+// Calls of at most this many rounds of resident workgroups run every pass in one launch
+// (see bwd_all_kernel).
+constexpr uint32_t kMergeRounds = 48;
 
 template <int D>
 struct BShape {
@@ -423,16 +428,6 @@ __device__ __forceinline__ void dq_unit(const BwdArgs& a, int nqb, uint32_t work
   }
 }
 
-// One workgroup per unit; the ids the hardware sends to one XCD cover a contiguous
-// range of units.
-template <int D, bool PREFIX>
-__global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(const BwdArgs a, int nqb) {
-  using Sh = BShape<D>;
-  __shared__ __attribute__((aligned(1024))) uint16_t sK[2][Sh::kTileElems];
-  __shared__ __attribute__((aligned(1024))) uint16_t sV[2][Sh::kTileElems];
-  dq_unit<D, PREFIX>(a, nqb, xcd_remap(blockIdx.x, a.n_wg_q), sK, sV);
-}
-
 // fn(integral_constant<int, i>) for i = 0 .. N-1, in order.
 template <int N, int I = 0, typename Fn>
 __device__ __forceinline__ void static_for(Fn&& fn) {
@@ -694,53 +689,97 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, int nkb, uint32_t wo
   }
 }
 
-// One workgroup per unit, as in the query-side pass. (The unit body is a separate
-// function in both passes; compiled so, the d = 128 dK pass fits 256 VGPRs without the
-// two spilled registers it had as one kernel body, 1.2% faster.)
+// One pass per launch: each XCD (the workgroups with blockIdx % 8 == x) runs a contiguous
+// share of the pass's units. (The unit bodies are separate functions; compiled so, the
+// d = 128 dK pass fits 256 VGPRs without the two spilled registers it had as one kernel
+// body, 1.2% faster.)
+template <int D, bool PREFIX>
+__global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(const BwdArgs a, int nblk) {
+  using Sh = BShape<D>;
+  __shared__ __attribute__((aligned(1024))) uint16_t sK[2][Sh::kTileElems];
+  __shared__ __attribute__((aligned(1024))) uint16_t sV[2][Sh::kTileElems];
+  dq_unit<D, PREFIX>(a, nblk, xcd_remap(blockIdx.x, a.n_wg_q), sK, sV);
+}
+
 template <int D, bool PREFIX, int MODE>
-__global__ __launch_bounds__(kBwdThreads, 2) void bwd_dkdv_kernel(const BwdArgs a, int nkb) {
+__global__ __launch_bounds__(kBwdThreads, 2) void bwd_dkdv_kernel(const BwdArgs a, int nblk) {
   using Sh = BShape<D>;
   __shared__ __attribute__((aligned(1024))) uint16_t sQ[2][Sh::kTileElems];
   __shared__ __attribute__((aligned(1024))) uint16_t sG[2][Sh::kTileElems];
   __shared__ __attribute__((aligned(256))) float sL[2][kBlockK];
   __shared__ __attribute__((aligned(256))) float sD[2][kBlockK];
-  dkdv_unit<D, PREFIX, MODE>(a, nkb, xcd_remap(blockIdx.x, a.n_wg_k), sQ, sG, sL, sD);
+  dkdv_unit<D, PREFIX, MODE>(a, nblk, xcd_remap(blockIdx.x, a.n_wg_k), sQ, sG, sL, sD);
+}
+
+// All passes in one launch, for calls of few rounds of workgroups: XCD x runs its share of
+// the key side's units, then of the query side's (at d = 128 the dK pass, dq, then the dV
+// pass), longest units first. As launches of their own each pass ends on a ragged round
+// with most slots empty, and a small call takes the sum of the passes' latencies. Measured
+// (launches of their own -> one launch, same process): B = 2, H = 4, 5 x 257 tokens at
+// d = 96, col g = 1 47.7 -> 38.1 us; H = 8, 10 x 700 at d = 64 137 -> 121 us; H = 6, 8 x 3600
+// at d = 128 2.304 -> 2.196 ms; H = 6, 24 x 3600 at d = 96, sym (25 rounds) 6.53 -> 6.40 ms;
+// H = 12 col (40 rounds) 8.51 -> 8.43 ms. Over many rounds the seam is nothing and the
+// shared kernel costs (H = 24 col, 80 rounds: 16.58 -> 16.68 ms), so longer calls keep a
+// launch per pass.
+template <int D, bool PREFIX>
+__global__ __launch_bounds__(kBwdThreads, 2) void bwd_all_kernel(const BwdArgs a, int nblk) {
+  using Sh = BShape<D>;
+  __shared__ __attribute__((aligned(1024))) uint16_t s0[2][Sh::kTileElems];
+  __shared__ __attribute__((aligned(1024))) uint16_t s1[2][Sh::kTileElems];
+  __shared__ __attribute__((aligned(256))) float sL[2][kBlockK];
+  __shared__ __attribute__((aligned(256))) float sD[2][kBlockK];
+  const uint32_t x = blockIdx.x % 8;
+  const uint32_t k0 = share_start(a.n_wg_k, x), nk = share_count(a.n_wg_k, x);
+  const uint32_t q0 = share_start(a.n_wg_q, x), nq = share_count(a.n_wg_q, x);
+  uint32_t pos = blockIdx.x / 8;
+  if (pos < nk) {
+    dkdv_unit<D, PREFIX, split_key_pass<D>() ? kDkOnly : kDkDv>(a, nblk, k0 + pos, s0, s1, sL, sD);
+    return;
+  }
+  pos -= nk;
+  if (pos < nq) {
+    dq_unit<D, PREFIX>(a, nblk, q0 + pos, s0, s1);
+    return;
+  }
+  if constexpr (split_key_pass<D>()) {
+    pos -= nq;
+    if (pos < nk) dkdv_unit<D, PREFIX, kDvOnly>(a, nblk, k0 + pos, s0, s1, sL, sD);
+  }
 }
 
 // ---------------------------------------------------------------------------
-// Sum of the partials of split segments: one thread per (split segment, batch
-// entry, row, 8 consecutive d), rounded to bf16 (RNE). Partials are laid out
-// [slot][batch][L][d] with L = max(T, P) rows per slot (T without a prefix).
+// Sum of the partials of split segments, of dq, dk and dv in one launch (grid y picks the
+// tensor): one thread per (split segment, batch entry, row, 8 consecutive d), rounded to
+// bf16 (RNE). Partials are laid out [slot][batch][L][d] with L = max(T, P) rows per slot
+// (T without a prefix).
 template <int D>
-__global__ __launch_bounds__(256) void sum_partials_kernel(const float* __restrict__ ws,
-                                                           const int32_t* __restrict__ heavy,
-                                                           int n_heavy, int B, int H, int F, int T,
-                                                           int P, uint16_t* __restrict__ out) {
+__global__ __launch_bounds__(256) void sum_partials_kernel(const SumArgs a) {
   constexpr int kGroups = D / 8;
-  const int L = max(T, P);
+  const SumJob& job = a.job[blockIdx.y];
+  const int F = a.F, T = a.T, P = a.P, L = max(T, P);
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t per_seg = (size_t)B * L * kGroups;
-  if (idx >= per_seg * (size_t)n_heavy) return;
+  const size_t per_seg = (size_t)a.B * L * kGroups;
+  if (idx >= per_seg * (size_t)job.n_heavy) return;
   const int hv = (int)(idx / per_seg);
   const size_t r = idx - (size_t)hv * per_seg;
   const int grp = (int)(r % kGroups);
   const size_t row = r / kGroups;  // b * L + t
   const size_t b = row / L, t = row - b * L;
-  const int head = heavy[4 * hv], frame = heavy[4 * hv + 1];
-  const int slot0 = heavy[4 * hv + 2], np = heavy[4 * hv + 3];
+  const int head = job.heavy[4 * hv], frame = job.heavy[4 * hv + 1];
+  const int slot0 = job.heavy[4 * hv + 2], np = job.heavy[4 * hv + 3];
   const int seg0 = frame < F ? P + frame * T : 0, seg_len = frame < F ? T : P;
   if ((int)t >= seg_len) return;
-  const size_t slot_stride = (size_t)B * L;
+  const size_t slot_stride = (size_t)a.B * L;
   f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = {0.f, 0.f, 0.f, 0.f};
   for (int p = 0; p < np; ++p) {
     const f32x4* src =
-        reinterpret_cast<const f32x4*>(ws + ((size_t)(slot0 + p) * slot_stride + row) * D + 8 * grp);
+        reinterpret_cast<const f32x4*>(job.ws + ((size_t)(slot0 + p) * slot_stride + row) * D + 8 * grp);
     a0 += src[0];
     a1 += src[1];
   }
-  const size_t orow = (b * H + head) * ((size_t)P + (size_t)F * T) + seg0 + t;
+  const size_t orow = (b * a.H + head) * ((size_t)P + (size_t)F * T) + seg0 + t;
   const f32x8 x = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-  *reinterpret_cast<bf16x8*>(out + orow * D + 8 * grp) = __builtin_convertvector(x, bf16x8);
+  *reinterpret_cast<bf16x8*>(job.out + orow * D + 8 * grp) = __builtin_convertvector(x, bf16x8);
 }
 
 template <int D>
@@ -751,46 +790,41 @@ hipError_t prep_d(const PrepArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <int D>
-hipError_t dq_d(const BwdArgs& a, hipStream_t stream) {
-  const int nqb = (std::max(a.T, a.P) + kRowsPerWg - 1) / kRowsPerWg;
-  if (a.P > 0)
-    hipLaunchKernelGGL((bwd_dq_kernel<D, true>), dim3(a.n_wg_q), dim3(kBwdThreads), 0, stream, a, nqb);
-  else
-    hipLaunchKernelGGL((bwd_dq_kernel<D, false>), dim3(a.n_wg_q), dim3(kBwdThreads), 0, stream, a, nqb);
-  return hipGetLastError();
-}
-
-template <int D, bool PREFIX, int MODE>
-void dkdv_launch(const BwdArgs& a, int nkb, hipStream_t stream) {
-  hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX, MODE>), dim3(a.n_wg_k), dim3(kBwdThreads), 0, stream,
-                     a, nkb);
-}
-
 template <int D, bool PREFIX>
-void dkdv_passes(const BwdArgs& a, int nkb, hipStream_t stream) {
+void bwd_launches(const BwdArgs& a, int nblk, hipStream_t stream) {
+  const dim3 threads(kBwdThreads);
+  // The XCDs' shares of a pass differ by at most one unit, so three more positions than
+  // an eighth of all units cover the busiest.
+  const uint32_t passes_k = split_key_pass<D>() ? 2 : 1;
+  const uint32_t units = passes_k * a.n_wg_k + a.n_wg_q;
+  if (units <= kMergeRounds * 8u * (uint32_t)a.slots_per_xcd) {
+    hipLaunchKernelGGL((bwd_all_kernel<D, PREFIX>), dim3(8 * (units / 8 + 3)), threads, 0, stream, a, nblk);
+    return;
+  }
+  hipLaunchKernelGGL((bwd_dq_kernel<D, PREFIX>), dim3(a.n_wg_q), threads, 0, stream, a, nblk);
   if constexpr (split_key_pass<D>()) {
-    dkdv_launch<D, PREFIX, kDvOnly>(a, nkb, stream);
-    dkdv_launch<D, PREFIX, kDkOnly>(a, nkb, stream);
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX, kDvOnly>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX, kDkOnly>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
   } else {
-    dkdv_launch<D, PREFIX, kDkDv>(a, nkb, stream);
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX, kDkDv>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
   }
 }
 
 template <int D>
-hipError_t dkdv_d(const BwdArgs& a, hipStream_t stream) {
-  const int nkb = (std::max(a.T, a.P) + kRowsPerWg - 1) / kRowsPerWg;
-  if (a.P > 0) dkdv_passes<D, true>(a, nkb, stream);
-  else dkdv_passes<D, false>(a, nkb, stream);
+hipError_t bwd_d(const BwdArgs& a, hipStream_t stream) {
+  const int nblk = (std::max(a.T, a.P) + kRowsPerWg - 1) / kRowsPerWg;
+  if (a.P > 0) bwd_launches<D, true>(a, nblk, stream);
+  else bwd_launches<D, false>(a, nblk, stream);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t sum_d(const SumArgs& a, hipStream_t stream) {
-  const size_t threads = (size_t)a.n_heavy * a.B * std::max(a.T, a.P) * (D / 8);
+  int n_heavy = 0;
+  for (int j = 0; j < a.n_jobs; ++j) n_heavy = std::max(n_heavy, a.job[j].n_heavy);
+  const size_t threads = (size_t)n_heavy * a.B * std::max(a.T, a.P) * (D / 8);
   const size_t blocks = (threads + 255) / 256;
-  hipLaunchKernelGGL(sum_partials_kernel<D>, dim3((uint32_t)blocks), dim3(256), 0, stream, a.ws,
-                     a.heavy, a.n_heavy, a.B, a.H, a.F, a.T, a.P, a.out);
+  hipLaunchKernelGGL(sum_partials_kernel<D>, dim3((uint32_t)blocks, (uint32_t)a.n_jobs), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -809,8 +843,7 @@ int bwd_keys_per_workgroup(int) { return kRowsPerWg; }
   }
 
 hipError_t launch_bwd_prep(const PrepArgs& a, hipStream_t stream) { TA_DISPATCH_D(prep_d, a, stream) }
-hipError_t launch_bwd_dq(const BwdArgs& a, hipStream_t stream) { TA_DISPATCH_D(dq_d, a, stream) }
-hipError_t launch_bwd_dkdv(const BwdArgs& a, hipStream_t stream) { TA_DISPATCH_D(dkdv_d, a, stream) }
+hipError_t launch_bwd(const BwdArgs& a, hipStream_t stream) { TA_DISPATCH_D(bwd_d, a, stream) }
 hipError_t launch_sum_partials(const SumArgs& a, hipStream_t stream) { TA_DISPATCH_D(sum_d, a, stream) }
 
 #undef TA_DISPATCH_D

@@ -770,31 +770,26 @@ int run_bwd(const void* q, const void* k, const void* v, const void* out, const 
   a.scale = scale;
   a.n_wg_q = (uint32_t)((int64_t)B * wq->n_items * nqb);
   a.n_wg_k = (uint32_t)((int64_t)B * wk->n_items * nkb);
-  e = ta::launch_bwd_dq(a, s);
-  if (e != hipSuccess) return fail(TA_ERR_HIP, std::string("dq launch: ") + hipGetErrorString(e));
-  e = ta::launch_bwd_dkdv(a, s);
-  if (e != hipSuccess) return fail(TA_ERR_HIP, std::string("dk/dv launch: ") + hipGetErrorString(e));
-  auto sum = [&](const DeviceWorkList* wl, const float* part, void* dst, const char* what) -> int {
-    if (wl->n_heavy == 0) return TA_OK;
-    ta::SumArgs m;
-    m.ws = part;
-    m.heavy = wl->heavy;
-    m.n_heavy = wl->n_heavy;
-    m.B = B;
-    m.H = H;
-    m.F = F;
-    m.T = T;
-    m.d = d;
-    m.P = P;
-    m.out = static_cast<uint16_t*>(dst);
-    hipError_t err = ta::launch_sum_partials(m, s);
-    if (err != hipSuccess)
-      return fail(TA_ERR_HIP, std::string(what) + " sum launch: " + hipGetErrorString(err));
-    return TA_OK;
+  a.slots_per_xcd = resident_slots_per_xcd(dev);
+  e = ta::launch_bwd(a, s);
+  if (e != hipSuccess) return fail(TA_ERR_HIP, std::string("gradient launch: ") + hipGetErrorString(e));
+  ta::SumArgs m;
+  m.n_jobs = 0;
+  m.B = B;
+  m.H = H;
+  m.F = F;
+  m.T = T;
+  m.d = d;
+  m.P = P;
+  auto add_sum = [&](const DeviceWorkList* wl, const float* part, void* dst) {
+    if (wl->n_heavy > 0)
+      m.job[m.n_jobs++] = ta::SumJob{part, wl->heavy, wl->n_heavy, static_cast<uint16_t*>(dst)};
   };
-  if ((st = sum(wq, ws_dq, dq, "dq")) != TA_OK) return st;
-  if ((st = sum(wk, ws_dk, dk, "dk")) != TA_OK) return st;
-  if ((st = sum(wk, ws_dv, dv, "dv")) != TA_OK) return st;
+  add_sum(wq, ws_dq, dq);
+  add_sum(wk, ws_dk, dk);
+  add_sum(wk, ws_dv, dv);
+  if (m.n_jobs > 0 && (e = ta::launch_sum_partials(m, s)) != hipSuccess)
+    return fail(TA_ERR_HIP, std::string("sum launch: ") + hipGetErrorString(e));
   g_last_error.clear();
   return TA_OK;
 }

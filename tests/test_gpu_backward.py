@@ -440,3 +440,33 @@ def test_calls_of_growing_size_share_one_stream_without_waits():
         ref = ob.attention_backward(qb, kb, vb, gb, mask, T, scale)
         for name, a, r in zip(("dq", "dk", "dv"), grads, ref):
             assert_grad(from_dev(a), r, f"stream-{name}")
+
+
+@pytest.mark.parametrize("d", [64, 96, 128])
+@pytest.mark.parametrize("P", [0, 40])
+def test_bwd_launch_per_pass_matches_one_launch_bitwise(d, P):
+    # Nine batch entries are some 70 rounds of workgroups (a launch per pass), one entry 8
+    # (all passes in one launch); the plan and the order of every sum are the same, so the
+    # gradients are too, bit for bit. T = 257 ends on a one-row block.
+    B, H, F, T = 9, 48, 13, 257
+    S = P + F * T
+    gen = torch.Generator(device="cuda").manual_seed(d + P)
+    q, k, v, g = (torch.randn((B, H, S, d), generator=gen, device="cuda").to(torch.bfloat16)
+                  for _ in range(4))
+    mask = om.tile_mask(F, 1, "sym")
+    s = torch.cuda.current_stream()
+    out = torch.empty_like(q)
+    lse = torch.empty((B, H, S), dtype=torch.float32, device="cuda")
+    dims = (H, F, T, P, d) if P else (H, F, T, d)
+    fwd = ta.tile_attn_fwd_mmdit if P else ta.tile_attn_fwd_heads
+    bwd = ta.tile_attn_bwd_mmdit if P else ta.tile_attn_bwd
+    fwd(q, k, v, out, B, *dims, mask, d ** -0.5, lse, s)
+    whole = [torch.full_like(q, float("nan")) for _ in range(3)]
+    bwd(q, k, v, out, g, lse, *whole, B, *dims, mask, d ** -0.5, s)
+    for b in (0, 4, 8):
+        print(f"[case] bwd launches d={d} P={P} b={b}", flush=True)
+        one = [torch.full_like(q[b], float("nan")) for _ in range(3)]
+        bwd(q[b], k[b], v[b], out[b], g[b], lse[b], *one, 1, *dims, mask, d ** -0.5, s)
+        for x, y in zip(whole, one):
+            assert bool(torch.isfinite(x[b].float()).all())
+            assert torch.equal(x[b], y)
