@@ -24,6 +24,10 @@ HIP_FLAGS = [
     "-mcode-object-version=5",
     # keep the compiler from emitting packed fp32 arithmetic (v_pk_*_f32)
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # matrix instructions write VGPRs unless an accumulator is asked for in AGPRs: in kernels
+    # of more than 256 registers the default keeps every result in AGPRs and copies each
+    # score out of them
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-I", os.path.join(REPO_DIR, "include"),
 ]
 

@@ -66,18 +66,22 @@ constexpr int kBwdThreads = 64 * kBwdWaves;
 // pass needs more than 256 registers and runs one workgroup per CU.
 constexpr int kRowsPerWg = kBwdWaves * 32;
 
-// What one launch of the key-side kernel produces. At d = 128 dK and dV together
-// (their accumulators, K and V operands alone take 192 registers) need one workgroup
-// per CU with the scores copied out of AGPRs; two passes that each fit 256 VGPRs
-// (dV: S and P only; dK: S, dP and dS) run at two workgroups per CU and, although
-// they form S twice (40 products instead of 32), take less time.
+// What one pass of the key side produces. At d = 128 dK and dV together do not fit 256
+// VGPRs (their accumulators, K and V operands alone take 192): in the shared launch of
+// small calls, whose kernel runs at two workgroups per CU, the key side is two passes
+// there (dV: S and P only; dK: S, dP and dS) that form S twice; larger calls run
+// dkdv_roll_unit.
 enum KeyPass { kDkDv = 0, kDvOnly = 1, kDkOnly = 2 };
 template <int D>
 constexpr bool split_key_pass() { return D == 128; }
 
 // Calls of at most this many rounds of resident workgroups run every pass in one launch
-// (see bwd_all_kernel).
-constexpr uint32_t kMergeRounds = 48;
+// (see bwd_all_kernel). At d = 128 the shared launch forms S twice on the key side, which
+// the kernel of its own does not (see dkdv_roll_unit): they meet at 3 to 4 rounds (H = 4,
+// 10 x 700 tokens, col g = 1, 2 rounds: 104 us in one launch, 118 in two; H = 8, g = 2:
+// 235 and 233; H = 16: 447 and 430; H = 24, 12 x 900, sym: 2.11 and 1.87 ms).
+template <int D>
+constexpr uint32_t merge_rounds() { return D == 128 ? 3 : 48; }
 
 template <int D>
 struct BShape {
@@ -689,6 +693,311 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, int nkb, uint32_t wo
   }
 }
 
+// ---------------------------------------------------------------------------
+// dk/dv pass at d = 128, one wave per SIMD.
+//
+// dK, dV (128 registers), the K and V operands (64) and the scores of a 32-key block do not
+// fit 256 VGPRs together, and as two passes (dV, dK) S is formed twice. This kernel
+// runs one 4-wave workgroup per compute unit with 512 registers per wave: the accumulators
+// stay in AGPRs, everything the vector ALU touches in VGPRs, and S is formed once (four
+// products instead of five). With one wave per SIMD nothing else hides a stall, so each
+// wave runs one unbroken stream of matrix instructions over 32-query blocks:
+//   body h:  S, dP of block h          | P, dS of block h - 1, second half of its queries
+//            dV, dK update of h - 1    | P, dS of block h, first half
+// with the vector work dealt out a few instructions per MFMA, every operand fragment read
+// kAhead packets ahead across the phases, and the blocks in a ring of kRing LDS slots, five
+// blocks loaded ahead, so that one barrier per two blocks suffices and never waits for the
+// block it is about to use. (MFMA 47% busy at 1.99 GHz as a plain tile loop, 60% at
+// 1.84 GHz as this stream.) Measured at the 93-frame shape, H = 18, col g = 1, the dk/dv
+// pass 12.55 -> 9.81 ms.
+
+// This lane's id, read where it is called (an asm statement the compiler cannot hoist):
+// the epilogues derive their rows from it, so no row address is held in vector registers
+// across a tile loop.
+__device__ __forceinline__ int fresh_lane() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
+}
+
+// acc += a b with the accumulator kept in AGPRs. The compiler does not track the hazards of
+// an asm MFMA; here none can arise: a comes from LDS (its wait counts asm operands), b was
+// written by the vector ALU at least one MFMA earlier, and acc is read by nothing but these
+// MFMAs, the next on the same accumulator 2 D/32 - 1 others later, until the drain after the
+// loop.
+__device__ __forceinline__ void mfma_acc(bf16x8 a, bf16x8 b, f32x16& acc) {
+  asm("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+
+constexpr int kRing = 8;
+// Elements of a ring slot: the 32-row Q and dO blocks, lse2 and -delta (64 floats each, the
+// first 32 used).
+template <int D>
+constexpr int roll_slot() { return 2 * 32 * D + 256; }
+
+template <int D, bool PREFIX>
+__device__ __forceinline__ void dkdv_roll_unit(const BwdArgs& a, int nkb, uint32_t work, uint16_t* ring) {
+  using Sh = BShape<D>;
+  constexpr int kC = Sh::kChunks, kMb = Sh::kDBlocks;
+  constexpr int kBlk = 32 * D;              // elements of a 32-row block of one tensor
+  constexpr int kSlot = roll_slot<D>();
+  constexpr int kLd = kBlk * 2 / 2048;      // tile loads per wave and block (two waves per tensor)
+  constexpr int kAhead = 3;
+  const uint32_t per_b = (uint32_t)a.n_items_k * (uint32_t)nkb;
+  const uint32_t b = work / per_b;
+  const uint32_t rem = work - b * per_b;
+  const int32_t* item = a.items_k + 5 * (rem / nkb);
+  const uint32_t bh = b * (uint32_t)a.H + (uint32_t)item[0];
+  const int frame = item[1], qbeg = item[2], n_keep = item[3], slot = item[4];
+  const int kblk = (int)(rem % nkb);
+  const int T = a.T;
+  const Layout<PREFIX> lay{a.F, T, a.P};
+  const int seg0 = lay.start(frame), seg_len = lay.len(frame);
+  if (PREFIX && kblk * kRowsPerWg >= seg_len) return;
+
+  const size_t head_rows = (size_t)a.P * PREFIX + (size_t)a.F * T;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row0 = kblk * kRowsPerWg + wave * 32;  // this wave's first key of the segment
+
+  // This lane's key as B operand of S = Q K^T and dP = dO V^T.
+  bf16x8 kf[kC], vf[kC];
+  f32x16 dk[kMb], dv[kMb];
+  {
+    const int lane = fresh_lane(), krow = row0 + (lane & 31);
+    const size_t kr = (size_t)bh * head_rows + seg0 + krow;
+    load_row_operand<D>(a.k + kr * D, krow < seg_len, a.keep, a.flip, lane >> 5, kf);
+    load_row_operand<D>(a.v + kr * D, krow < seg_len, ~0u, 0u, lane >> 5, vf);
+  }
+#pragma unroll
+  for (int mb = 0; mb < kMb; ++mb) dk[mb] = dv[mb] = f32x16{};
+
+  const int bpf = (T + 31) / 32;
+  int nb = n_keep * bpf;  // 32-query blocks
+  if constexpr (PREFIX) {
+    if (n_keep > 0 && a.cols_k[qbeg + n_keep - 1] == a.F) nb += (a.P + 31) / 32 - bpf;
+  }
+  if (nb > 0) {
+    const int lane = fresh_lane();
+    const int hf = lane >> 5;
+    RowAddr<D> ra;
+    ra.init(lane & 31, hf);
+    TrAddr<D> ta;
+    ta.init(lane);
+    // Waves 0 and 1 load the Q blocks (half a block each) and lse2, waves 2 and 3 dO and
+    // -delta. Both waves of a tensor load the same row values, so that every wave has the
+    // same number of loads in flight.
+    const bool second = wave >= 2;
+    const uint16_t* src = (second ? a.dout : a.q) + bh * head_rows * D;
+    const float* lsrc = (second ? a.ndelta : a.lse2) + bh * head_rows;
+    int off[kLd];
+#pragma unroll
+    for (int j = 0; j < kLd; ++j) {
+      const int q = 64 * ((wave & 1) * kLd + j) + lane;
+      const int r = q / Sh::kPieces, ps = q % Sh::kPieces;
+      off[j] = (r * D + 8 * (ps ^ dsw<D>(r))) * 2;
+    }
+    const uint32_t lds_dst = lds_addr(ring) + (second ? kBlk * 2 : 0) + (wave & 1) * kLd * 1024;
+    const uint32_t lds_row_dst = lds_addr(ring) + 4 * kBlk + (second ? 256 : 0);
+    // The block to load next: its rows start at src / lsrc, `left` rows of its segment
+    // remain (0 past the last block: those loads write zeros), at ring byte offset ld_off.
+    // The kept list is read with scalar loads.
+    using ColsPtr = const __attribute__((address_space(4))) int32_t*;
+    const ColsPtr cols = (ColsPtr)(a.cols_k + qbeg);
+    int ld_e = 0, left = lay.len(cols[0]);
+    uint32_t ld_off = 0;
+    {
+      const int64_t r0 = lay.start(cols[0]);
+      src += r0 * D;
+      lsrc += r0;
+    }
+    // (buffer_words without its readfirstlanes: everything here is scalar already)
+    auto words = [](const void* p, uint32_t bytes) {
+      const uint64_t x = reinterpret_cast<uint64_t>(p);
+      return i32x4{(int)(uint32_t)x, (int)(uint32_t)(x >> 32), (int)bytes, 0x00020000};
+    };
+    auto load_part = [&](int j) {
+      load_to_lds(words(src, (uint32_t)(min(left, 32) * D * 2)), lds_dst + ld_off + 1024u * j, off[j]);
+    };
+    auto load_rows = [&]() {
+      load_dword_to_lds(words(lsrc, (uint32_t)(min(left, 32) * 4)), lds_row_dst + ld_off, 4 * lane);
+    };
+    auto load_advance = [&]() {
+      ld_off = ld_off == (kRing - 1) * kSlot * 2 ? 0 : ld_off + kSlot * 2;
+      src += 32 * D;
+      lsrc += 32;
+      left -= 32;
+      if (left <= 0) {
+        left = 0;
+        if (++ld_e < n_keep) {
+          const int j = cols[ld_e];
+          const size_t r0 = (size_t)bh * head_rows + lay.start(j);
+          src = (second ? a.dout : a.q) + r0 * D;
+          lsrc = (second ? a.ndelta : a.lse2) + r0;
+          left = lay.len(j);
+        }
+      }
+    };
+    // Blocks 0 .. 4 in flight, block 0 visible.
+#pragma unroll
+    for (int j = 0; j < 5; ++j) {
+      if (j > 0) load_advance();
+#pragma unroll
+      for (int i = 0; i < kLd; ++i) load_part(i);
+      load_rows();
+    }
+    wait_loads<4 * (kLd + 1)>();
+    __syncthreads();
+
+    // By block parity: S and dP - delta, P and dS of the first 16 query entries (queries
+    // 16 c2 + 8u + 4 hf + j are entries 8 c2 + 4u + j); p1, d1 of the second.
+    f32x16 sc[2], dp[2];
+    bf16x8 p0[2], d0[2], p1, d1;
+    auto row_values = [&](const uint16_t* at, int first, f32x4& lo, f32x4& hi) {
+      const float* L = reinterpret_cast<const float*>(at + 2 * kBlk) + first + 4 * hf;
+      lo = *reinterpret_cast<const f32x4*>(L);
+      hi = *reinterpret_cast<const f32x4*>(L + 8);
+    };
+    // P and dS of entries 8 c2 .. 8 c2 + 7, as a list of 10 steps per pair of entries (an
+    // exponential counts two) dealt out evenly to n packets; packet i's share.
+    float t0, t1, y0, y1;
+    auto vec_share = [&](auto parc, auto c2c, auto ic, auto nc, const f32x4(&l4)[2]) {
+      constexpr int par = decltype(parc)::value, c2 = decltype(c2c)::value, i = decltype(ic)::value,
+                    n = decltype(nc)::value;
+      if constexpr (i >= 0) {
+#pragma unroll
+        for (int m = i * 40 / n; m < (i + 1) * 40 / n; ++m) {
+          const int op = m % 10, e = 8 * c2 + 2 * (m / 10), w = (e % 8) / 2;
+          if (op == 0) t0 = __builtin_fmaf(sc[par][e], a.c, -l4[(e % 8) / 4][e % 4]);
+          if (op == 1) t1 = __builtin_fmaf(sc[par][e + 1], a.c, -l4[(e % 8) / 4][e % 4 + 1]);
+          if (op == 2) t0 = __builtin_amdgcn_fmed3f(fast_exp2(t0), 0.f, 1.f);  // as prob()
+          if (op == 4) t1 = __builtin_amdgcn_fmed3f(fast_exp2(t1), 0.f, 1.f);
+          if (op == 6) y0 = t0 * dp[par][e];
+          if (op == 7) y1 = t1 * dp[par][e + 1];
+          if (op >= 8) {
+            const f32x2 v = op == 8 ? f32x2{t0, t1} : f32x2{y0, y1};
+            bf16x8& dst = op == 8 ? (c2 ? p1 : p0[par]) : (c2 ? d1 : d0[par]);
+            u32x4 x = __builtin_bit_cast(u32x4, dst);
+            x[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+            dst = __builtin_bit_cast(bf16x8, x);
+          }
+        }
+      }
+    };
+    constexpr int kNA = 2 * kC, kNU = 4 * kMb;  // fragments (= MFMAs) of the two phases
+    auto frag_a = [&](const uint16_t* at, auto ic) -> bf16x8 {
+      constexpr int i = decltype(ic)::value;
+      return as_bf16x8(load16(at + (i < kC ? ra.get(i) : kBlk + ra.get(i - kC))));
+    };
+    auto frag_u = [&](const uint16_t* at, auto ic) -> bf16x8 {
+      constexpr int i = decltype(ic)::value, c2 = i / (2 * kMb), q = i % (2 * kMb);
+      return tr_frag<D>(at + (q % 2 ? 0 : kBlk), ta, q / 2, c2);
+    };
+    bf16x8 pf[kAhead];        // the first fragments of the next phase
+    uint32_t at_c = 0, at_p = 0;  // ring offsets (elements) of block h and of block h - 1
+    auto body = [&](auto parc) {
+      constexpr int par = decltype(parc)::value;
+      const uint32_t at_n = at_c == (kRing - 1) * kSlot ? 0 : at_c + kSlot;
+      const uint16_t *tc = ring + at_c, *tp = ring + at_p, *tn = ring + at_n;
+      f32x4 l4[2];
+      bf16x8 fr[kAhead + 1];
+      using ParC = std::integral_constant<int, par>;
+      using ParP = std::integral_constant<int, par ^ 1>;
+      row_values(tp, 16, l4[0], l4[1]);
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) fr[j] = pf[j];
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<kNA>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        if constexpr (i + kAhead < kNA) fr[(i + kAhead) % (kAhead + 1)] = frag_a(tc, std::integral_constant<int, i + kAhead>{});
+        else pf[i + kAhead - kNA] = frag_u(tp, std::integral_constant<int, i + kAhead - kNA>{});
+        if constexpr (i == kC - 2) {  // dP starts at the rows' -delta
+          f32x4 d4[4];
+          row_values(tc, 64, d4[0], d4[1]);
+          row_values(tc, 80, d4[2], d4[3]);
+#pragma unroll
+          for (int e = 0; e < 16; ++e) dp[par][e] = d4[e / 4][e % 4];
+        }
+        const bf16x8& f = fr[i % (kAhead + 1)];
+        if constexpr (i < kC) sc[par] = mfma32(f, kf[i], i == 0 ? f32x16{} : sc[par]);
+        else dp[par] = mfma32(f, vf[i - kC], dp[par]);
+        vec_share(ParP{}, std::integral_constant<int, 1>{}, std::integral_constant<int, i - 1>{},
+                  std::integral_constant<int, kNA - 1>{}, l4);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      // The asm statement keeps the compiler from sinking the packets' vector work past
+      // the branch in load_advance, to the first use of p1 and d1.
+      asm volatile("" : "+v"(p1), "+v"(d1));
+      load_advance();
+      if constexpr (par == 0) {
+        // Blocks h + 1 and h + 2 have landed (those of h + 3 and h + 4 may be in flight),
+        // for every wave once all are here; every wave is also done with block h - 2, so
+        // the slots of blocks h - 3 and h - 2 can take blocks h + 5 and h + 6.
+        wait_loads<2 * (kLd + 1)>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+      }
+      row_values(tc, 0, l4[0], l4[1]);
+#pragma unroll
+      for (int j = 0; j < kAhead; ++j) fr[j] = pf[j];
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<kNU>([&](auto ic) {
+        constexpr int i = decltype(ic)::value, c2 = i / (2 * kMb), q = i % (2 * kMb), mb = q / 2;
+        if constexpr (i + kAhead < kNU) fr[(i + kAhead) % (kAhead + 1)] = frag_u(tp, std::integral_constant<int, i + kAhead>{});
+        else pf[i + kAhead - kNU] = frag_a(tn, std::integral_constant<int, i + kAhead - kNU>{});
+        if constexpr (i >= 1 && i <= kLd) load_part(i - 1);
+        if constexpr (i == kLd + 1) load_rows();
+        const bf16x8& f = fr[i % (kAhead + 1)];
+        if constexpr (q % 2) mfma_acc(f, c2 ? d1 : d0[par ^ 1], dk[mb]);
+        else mfma_acc(f, c2 ? p1 : p0[par ^ 1], dv[mb]);
+        vec_share(ParC{}, std::integral_constant<int, 0>{}, std::integral_constant<int, i - 2>{},
+                  std::integral_constant<int, kNU - 2>{}, l4);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      asm volatile("" : "+v"(p0[par]), "+v"(d0[par]));
+      at_p = at_c;
+      at_c = at_n;
+    };
+    // Before block 0 there is nothing to update: its P and dS are zero (exp2(-inf)). Blocks
+    // nb and nb + 1 are zeros, so the bodies past the last block add exactly nothing.
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      sc[1][e] = -INFINITY;
+      dp[1][e] = 0.f;
+    }
+    p0[1] = d0[1] = as_bf16x8(u32x4{0u, 0u, 0u, 0u});
+    static_for<kAhead>([&](auto jc) { pf[decltype(jc)::value] = frag_a(ring, jc); });
+    for (int h = 0; h <= nb; h += 2) {
+      body(std::integral_constant<int, 0>{});
+      body(std::integral_constant<int, 1>{});
+    }
+    wait_tile_loads();
+  }
+
+  // The last MFMAs are done before the accumulators are read (16 passes at most).
+#pragma unroll
+  for (int mb = 0; mb < kMb; ++mb) asm volatile("s_nop 15\n\ts_nop 15" : "+a"(dk[mb]), "+a"(dv[mb]));
+  // dK uses the unflipped q of the LDS blocks, so scale (with its sign) applies.
+  const int lane = fresh_lane(), hf = lane >> 5, row = row0 + (lane & 31);
+  if (row < seg_len) {
+    if (slot < 0) {
+      const size_t at = ((size_t)bh * head_rows + seg0 + row) * D;
+      store_row_bf16<D>(a.dk + at, dk, a.scale, hf);
+      store_row_bf16<D>(a.dv + at, dv, 1.f, hf);
+    } else {
+      const int slot_rows = PREFIX ? max(T, a.P) : T;
+      const size_t at = (((size_t)slot * a.B + b) * slot_rows + row) * D;
+      store_row_f32<D>(a.ws_dk + at, dk, a.scale, hf);
+      store_row_f32<D>(a.ws_dv + at, dv, 1.f, hf);
+    }
+  }
+}
+
+template <int D, bool PREFIX>
+__global__ __launch_bounds__(kBwdThreads, 1) void bwd_dkdv_roll_kernel(const BwdArgs a, int nblk) {
+  __shared__ __attribute__((aligned(1024))) uint16_t ring[kRing * roll_slot<D>()];
+  dkdv_roll_unit<D, PREFIX>(a, nblk, xcd_remap(blockIdx.x, a.n_wg_k), ring);
+}
+
 // One pass per launch: each XCD (the workgroups with blockIdx % 8 == x) runs a contiguous
 // share of the pass's units. (The unit bodies are separate functions; compiled so, the
 // d = 128 dK pass fits 256 VGPRs without the two spilled registers it had as one kernel
@@ -701,14 +1010,14 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(const BwdArgs a,
   dq_unit<D, PREFIX>(a, nblk, xcd_remap(blockIdx.x, a.n_wg_q), sK, sV);
 }
 
-template <int D, bool PREFIX, int MODE>
+template <int D, bool PREFIX>
 __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dkdv_kernel(const BwdArgs a, int nblk) {
   using Sh = BShape<D>;
   __shared__ __attribute__((aligned(1024))) uint16_t sQ[2][Sh::kTileElems];
   __shared__ __attribute__((aligned(1024))) uint16_t sG[2][Sh::kTileElems];
   __shared__ __attribute__((aligned(256))) float sL[2][kBlockK];
   __shared__ __attribute__((aligned(256))) float sD[2][kBlockK];
-  dkdv_unit<D, PREFIX, MODE>(a, nblk, xcd_remap(blockIdx.x, a.n_wg_k), sQ, sG, sL, sD);
+  dkdv_unit<D, PREFIX, kDkDv>(a, nblk, xcd_remap(blockIdx.x, a.n_wg_k), sQ, sG, sL, sD);
 }
 
 // All passes in one launch, for calls of few rounds of workgroups: XCD x runs its share of
@@ -720,7 +1029,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dkdv_kernel(const BwdArgs 
 // at d = 128 2.304 -> 2.196 ms; H = 6, 24 x 3600 at d = 96, sym (25 rounds) 6.53 -> 6.40 ms;
 // H = 12 col (40 rounds) 8.51 -> 8.43 ms. Over many rounds the seam is nothing and the
 // shared kernel costs (H = 24 col, 80 rounds: 16.58 -> 16.68 ms), so longer calls keep a
-// launch per pass.
+// launch per pass (merge_rounds).
 template <int D, bool PREFIX>
 __global__ __launch_bounds__(kBwdThreads, 2) void bwd_all_kernel(const BwdArgs a, int nblk) {
   using Sh = BShape<D>;
@@ -797,16 +1106,15 @@ void bwd_launches(const BwdArgs& a, int nblk, hipStream_t stream) {
   // an eighth of all units cover the busiest.
   const uint32_t passes_k = split_key_pass<D>() ? 2 : 1;
   const uint32_t units = passes_k * a.n_wg_k + a.n_wg_q;
-  if (units <= kMergeRounds * 8u * (uint32_t)a.slots_per_xcd) {
+  if (units <= merge_rounds<D>() * 8u * (uint32_t)a.slots_per_xcd) {
     hipLaunchKernelGGL((bwd_all_kernel<D, PREFIX>), dim3(8 * (units / 8 + 3)), threads, 0, stream, a, nblk);
     return;
   }
   hipLaunchKernelGGL((bwd_dq_kernel<D, PREFIX>), dim3(a.n_wg_q), threads, 0, stream, a, nblk);
   if constexpr (split_key_pass<D>()) {
-    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX, kDvOnly>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
-    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX, kDkOnly>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
+    hipLaunchKernelGGL((bwd_dkdv_roll_kernel<D, PREFIX>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
   } else {
-    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX, kDkDv>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
   }
 }
 

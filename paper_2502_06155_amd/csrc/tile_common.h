@@ -156,6 +156,10 @@ __device__ __forceinline__ void load_dword_to_lds(i32x4 rsrc, uint32_t lds, int 
 // Waits until every buffer load of this wave, including those writing LDS, is done.
 __device__ __forceinline__ void wait_tile_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// Waits until at most N of this wave's buffer loads are in flight (they finish in order).
+template <int N>
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
 __device__ __forceinline__ uint32_t lds_addr(const uint16_t* p) {
   return __builtin_amdgcn_readfirstlane(
       (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) uint16_t*)p));

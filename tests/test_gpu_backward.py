@@ -446,9 +446,10 @@ def test_calls_of_growing_size_share_one_stream_without_waits():
 @pytest.mark.parametrize("P", [0, 40])
 def test_bwd_launch_per_pass_matches_one_launch_bitwise(d, P):
     # Nine batch entries are some 70 rounds of workgroups (a launch per pass), one entry 8
-    # (all passes in one launch); the plan and the order of every sum are the same, so the
-    # gradients are too, bit for bit. T = 257 ends on a one-row block.
-    B, H, F, T = 9, 48, 13, 257
+    # (all passes in one launch; at d = 128, where the line lies at 3 rounds, 18 and 2); the
+    # plan and the order of every sum are the same, so the gradients are too, bit for bit.
+    # T = 257 ends on a one-row block.
+    B, H, F, T = 9, 8 if d == 128 else 48, 13, 257
     S = P + F * T
     gen = torch.Generator(device="cuda").manual_seed(d + P)
     q, k, v, g = (torch.randn((B, H, S, d), generator=gen, device="cuda").to(torch.bfloat16)
