@@ -36,6 +36,7 @@ struct DeviceWorkList {
   const int32_t* cut_units = nullptr;
   int n_cut_units = 0, n_part_slots = 0, wg_per_xcd = 0;
   bool unit_table = false;  // every position is a table entry (no contiguous whole units)
+  uint32_t share[9] = {};   // the XCDs' contiguous shares of the units (unit_shares)
 };
 
 // The same plan as host words, before upload: offsets of the parts in words.
@@ -46,10 +47,17 @@ struct HostWorkList {
   size_t off_xcd = 0, off_pieces = 0, off_cut_units = 0;
   int n_cut_units = 0, n_part_slots = 0, wg_per_xcd = 0;
   bool unit_table = false;
+  uint32_t share[9] = {};
 };
 
 // Workgroups a forward launch keeps resident per XCD (two per compute unit).
 int resident_slots_per_xcd(int dev);
+
+// Deals the units (b, item, block of `rows` rows; nblk blocks per segment) of hw out to the
+// eight XCDs as contiguous shares: XCD x gets [share[x], share[x + 1]). By count where that
+// is even to within 3% of the work, else by work (kept 64-token tiles, half for a block of
+// at most 32 rows, which takes about half a full block's time).
+void unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, uint32_t share[9]);
 
 // Appends the forward launch schedule to hw (see FwdArgs::sched): B batch entries, nqb
 // query blocks of `rows` rows per segment, head dimension d, T tokens per frame and P

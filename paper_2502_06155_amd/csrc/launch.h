@@ -39,6 +39,7 @@ struct FwdArgs {
   // tile, tiles, partial slot (-1: a whole unit)}; and per unit run in parts {unit,
   // first partial slot, parts}. Units are (b, item, query block), query block fastest.
   const int32_t* sched;
+  uint32_t share[9];    // without a table, XCD x runs the units [share[x], share[x + 1])
   const int32_t* cut_units;
   int n_cut_units;
   int wg_per_xcd;       // queue positions of the busiest XCD
@@ -112,6 +113,8 @@ struct BwdArgs {
   uint32_t keep;     // 0 zeroes that operand (scale 0), else ~0
   uint32_t n_wg_q;   // B * n_items_q * ceil(max(T, P) / bwd_queries_per_workgroup(d))
   uint32_t n_wg_k;   // B * n_items_k * ceil(max(T, P) / bwd_keys_per_workgroup(d))
+  // The XCDs' contiguous shares of each side's units: XCD x runs [share[x], share[x + 1]).
+  uint32_t share_q[9], share_k[9];
   int slots_per_xcd;  // workgroups of the gradient kernels resident per XCD
 };
 

@@ -62,8 +62,8 @@ constexpr int kBwdThreads = 64 * kBwdWaves;
 // the other's matrix instructions. Measured at the 93-frame shape this beats 64
 // rows per wave at one workgroup per CU (which halves the LDS fragment reads per
 // MFMA but puts the accumulators in AGPRs, copies the scores out of them and
-// serialises the vector work) by 17% (dq) and 12% (dk/dv). At d = 128 the dk/dv
-// pass needs more than 256 registers and runs one workgroup per CU.
+// serialises the vector work) by 17% (dq) and 12% (dk/dv). Both passes at d = 128 as well
+// own 32 rows per wave; large calls run the dk/dv pass with one wave per SIMD there.
 constexpr int kRowsPerWg = kBwdWaves * 32;
 
 // What one pass of the key side produces. At d = 128 dK and dV together do not fit 256
@@ -995,7 +995,8 @@ __device__ __forceinline__ void dkdv_roll_unit(const BwdArgs& a, int nkb, uint32
 template <int D, bool PREFIX>
 __global__ __launch_bounds__(kBwdThreads, 1) void bwd_dkdv_roll_kernel(const BwdArgs a, int nblk) {
   __shared__ __attribute__((aligned(1024))) uint16_t ring[kRing * roll_slot<D>()];
-  dkdv_roll_unit<D, PREFIX>(a, nblk, xcd_remap(blockIdx.x, a.n_wg_k), ring);
+  const uint32_t x = blockIdx.x % 8, u = a.share_k[x] + blockIdx.x / 8;
+  if (u < a.share_k[x + 1]) dkdv_roll_unit<D, PREFIX>(a, nblk, u, ring);
 }
 
 // One pass per launch: each XCD (the workgroups with blockIdx % 8 == x) runs a contiguous
@@ -1007,7 +1008,8 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(const BwdArgs a,
   using Sh = BShape<D>;
   __shared__ __attribute__((aligned(1024))) uint16_t sK[2][Sh::kTileElems];
   __shared__ __attribute__((aligned(1024))) uint16_t sV[2][Sh::kTileElems];
-  dq_unit<D, PREFIX>(a, nblk, xcd_remap(blockIdx.x, a.n_wg_q), sK, sV);
+  const uint32_t x = blockIdx.x % 8, u = a.share_q[x] + blockIdx.x / 8;
+  if (u < a.share_q[x + 1]) dq_unit<D, PREFIX>(a, nblk, u, sK, sV);
 }
 
 template <int D, bool PREFIX>
@@ -1017,7 +1019,8 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dkdv_kernel(const BwdArgs 
   __shared__ __attribute__((aligned(1024))) uint16_t sG[2][Sh::kTileElems];
   __shared__ __attribute__((aligned(256))) float sL[2][kBlockK];
   __shared__ __attribute__((aligned(256))) float sD[2][kBlockK];
-  dkdv_unit<D, PREFIX, kDkDv>(a, nblk, xcd_remap(blockIdx.x, a.n_wg_k), sQ, sG, sL, sD);
+  const uint32_t x = blockIdx.x % 8, u = a.share_k[x] + blockIdx.x / 8;
+  if (u < a.share_k[x + 1]) dkdv_unit<D, PREFIX, kDkDv>(a, nblk, u, sQ, sG, sL, sD);
 }
 
 // All passes in one launch, for calls of few rounds of workgroups: XCD x runs its share of
@@ -1038,8 +1041,8 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_all_kernel(const BwdArgs a
   __shared__ __attribute__((aligned(256))) float sL[2][kBlockK];
   __shared__ __attribute__((aligned(256))) float sD[2][kBlockK];
   const uint32_t x = blockIdx.x % 8;
-  const uint32_t k0 = share_start(a.n_wg_k, x), nk = share_count(a.n_wg_k, x);
-  const uint32_t q0 = share_start(a.n_wg_q, x), nq = share_count(a.n_wg_q, x);
+  const uint32_t k0 = a.share_k[x], nk = a.share_k[x + 1] - k0;
+  const uint32_t q0 = a.share_q[x], nq = a.share_q[x + 1] - q0;
   uint32_t pos = blockIdx.x / 8;
   if (pos < nk) {
     dkdv_unit<D, PREFIX, split_key_pass<D>() ? kDkOnly : kDkDv>(a, nblk, k0 + pos, s0, s1, sL, sD);
@@ -1102,19 +1105,24 @@ hipError_t prep_d(const PrepArgs& a, hipStream_t stream) {
 template <int D, bool PREFIX>
 void bwd_launches(const BwdArgs& a, int nblk, hipStream_t stream) {
   const dim3 threads(kBwdThreads);
-  // The XCDs' shares of a pass differ by at most one unit, so three more positions than
-  // an eighth of all units cover the busiest.
   const uint32_t passes_k = split_key_pass<D>() ? 2 : 1;
   const uint32_t units = passes_k * a.n_wg_k + a.n_wg_q;
+  uint32_t most_k = 0, most_q = 0, most_all = 0;  // positions of the busiest XCD
+  for (int x = 0; x < 8; ++x) {
+    const uint32_t nk = a.share_k[x + 1] - a.share_k[x], nq = a.share_q[x + 1] - a.share_q[x];
+    most_k = std::max(most_k, nk);
+    most_q = std::max(most_q, nq);
+    most_all = std::max(most_all, passes_k * nk + nq);
+  }
   if (units <= merge_rounds<D>() * 8u * (uint32_t)a.slots_per_xcd) {
-    hipLaunchKernelGGL((bwd_all_kernel<D, PREFIX>), dim3(8 * (units / 8 + 3)), threads, 0, stream, a, nblk);
+    hipLaunchKernelGGL((bwd_all_kernel<D, PREFIX>), dim3(8 * most_all), threads, 0, stream, a, nblk);
     return;
   }
-  hipLaunchKernelGGL((bwd_dq_kernel<D, PREFIX>), dim3(a.n_wg_q), threads, 0, stream, a, nblk);
+  hipLaunchKernelGGL((bwd_dq_kernel<D, PREFIX>), dim3(8 * most_q), threads, 0, stream, a, nblk);
   if constexpr (split_key_pass<D>()) {
-    hipLaunchKernelGGL((bwd_dkdv_roll_kernel<D, PREFIX>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
+    hipLaunchKernelGGL((bwd_dkdv_roll_kernel<D, PREFIX>), dim3(8 * most_k), threads, 0, stream, a, nblk);
   } else {
-    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX>), dim3(a.n_wg_k), threads, 0, stream, a, nblk);
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX>), dim3(8 * most_k), threads, 0, stream, a, nblk);
   }
 }
 

@@ -23,6 +23,7 @@
 #include "launch.h"
 #include "host_internal.h"
 #include "plan_cache.h"
+#include "unit_order.h"
 
 namespace ta {
 namespace host {
@@ -140,6 +141,61 @@ HostWorkList build_work_list(const uint8_t* masks, int n_masks, int H, int F, bo
   return hw;
 }
 
+// Why by work: with one mask per head, or fewer heads than XCDs under a sym mask, equal
+// counts hold unequal work and the launch lasts as long as the XCD with the most. Measured
+// (by count -> by work, same process): H = 6, 24 x 3600 at d = 96, one mask per head (sym
+// g = 2, sym g = 1, col g = 4) forward 3.435 -> 2.534 ms, gradients 9.71 -> 8.56 ms; sym g = 1
+// for all heads 1.867 -> 1.819 and 6.23 -> 5.98 ms. Launches whose counts are even (every
+// multiple of 8 heads under one mask) keep them, to the unit. Ordering each share longest
+// first as well gained nothing where it mattered (2.65 ms).
+void unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, uint32_t share[9]) {
+  const int32_t* items = hw.words.data();
+  const int32_t* cols = hw.words.data() + hw.off_cols;
+  const int64_t n_items = hw.n_items, per_b = n_items * nblk, n = B * per_b;
+  const int64_t tpf = (T + 63) / 64, ptiles = (P + 63) / 64;
+  for (uint32_t x = 0; x <= 8; ++x) share[x] = ta::share_start((uint32_t)n, x);
+  // Twice the work of item i's full blocks; its last block, and the blocks past its end.
+  auto tiles2 = [&](int64_t i) -> int64_t {
+    const int32_t* it = items + 5 * i;
+    const int beg = it[2], cnt = it[3];
+    int64_t t = cnt * tpf;
+    if (P > 0 && cnt > 0 && cols[beg + cnt - 1] == F) t += ptiles - tpf;
+    return 2 * t + 4;  // and a little for the block itself
+  };
+  auto unit2 = [&](int64_t i, int64_t blk) -> int64_t {
+    const int64_t left = (P > 0 && items[5 * i + 1] == F ? P : T) - blk * rows;
+    return left <= 0 ? 0 : left <= 32 ? tiles2(i) / 2 : tiles2(i);
+  };
+  std::vector<int64_t> before((size_t)n_items + 1, 0);  // work of the items before i
+  for (int64_t i = 0; i < n_items; ++i) {
+    const int64_t len = P > 0 && items[5 * i + 1] == F ? P : T;
+    const int64_t last = (len - 1) / rows;  // the last block with rows
+    before[i + 1] = before[i] + last * tiles2(i) + unit2(i, last);
+  }
+  const int64_t total = before[n_items];
+  auto work_before = [&](int64_t u) -> int64_t {
+    const int64_t b = u / per_b, i = (u % per_b) / nblk;
+    int64_t w = b * total + before[i];
+    for (int64_t blk = 0; blk < u % nblk; ++blk) w += unit2(i, blk);
+    return w;
+  };
+  if (n == 0 || total == 0) return;
+  int64_t most = 0;
+  for (int x = 0; x < 8; ++x) most = std::max(most, work_before(share[x + 1]) - work_before(share[x]));
+  if (most * 800 <= B * total * 103) return;  // most <= 1.03 * (B total / 8)
+  for (int x = 1; x < 8; ++x) {
+    const int64_t target = B * total / 8 * x, b = target / total, w = target - b * total;
+    int64_t i = std::upper_bound(before.begin(), before.end(), w) - before.begin() - 1;
+    int64_t u = 0;
+    for (int64_t at = before[i]; i < n_items && u < nblk && at + unit2(i, u) / 2 < w; ++u) at += unit2(i, u);
+    share[x] = (uint32_t)std::max<int64_t>(share[x - 1], std::min(n, b * per_b + i * nblk + u));
+  }
+  uint32_t positions = 0;  // the grid holds 8 times the longest share
+  for (int x = 0; x < 8; ++x) positions = std::max(positions, share[x + 1] - share[x]);
+  if ((int64_t)8 * positions * ta::kThreads > (int64_t)UINT32_MAX)
+    for (uint32_t x = 0; x <= 8; ++x) share[x] = ta::share_start((uint32_t)n, x);
+}
+
 DeviceWorkList place_work_list(const HostWorkList& hw, void* buf) {
   DeviceWorkList wl;
   const int32_t* w = static_cast<const int32_t*>(buf);
@@ -150,6 +206,7 @@ DeviceWorkList place_work_list(const HostWorkList& hw, void* buf) {
   wl.n_items = hw.n_items;
   wl.n_heavy = hw.n_heavy;
   wl.n_slots = hw.n_slots;
+  std::copy(hw.share, hw.share + 9, wl.share);
   if (hw.wg_per_xcd > 0) {
     wl.sched_xcd = w + hw.off_xcd;
     wl.cut_units = w + hw.off_cut_units;
@@ -196,11 +253,11 @@ void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int 
   // Longest first where it changes something: a plan with split frames runs the
   // kernel's persistent loop instead (its queue takes the natural order), and a share
   // whose units with rows already come longest first keeps the contiguous form.
-  const int64_t q = n / 8, r = n % 8;
+  unit_shares(hw, B, nqb, rows, T, P, F, hw.share);
   bool table = false;
   if (by_length && hw.n_heavy == 0) {
     for (int x = 0; x < 8 && !table; ++x) {
-      const int64_t start = x * q + std::min<int64_t>(x, r), cnt = q + (x < r);
+      const int64_t start = hw.share[x], cnt = hw.share[x + 1] - hw.share[x];
       int64_t prev = -1;
       for (int64_t u = start; u < start + cnt && !table; ++u) {
         if (!has_rows(u)) continue;
@@ -212,7 +269,7 @@ void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int 
   }
   std::vector<int64_t> us;
   for (int x = 0; x < 8; ++x) {
-    const int64_t start = x * q + std::min<int64_t>(x, r), cnt = q + (x < r);
+    const int64_t start = hw.share[x], cnt = hw.share[x + 1] - hw.share[x];
     int64_t n_dp = cnt;
     const int64_t first_piece = (int64_t)pieces.size() / 4;
     // This XCD's units in the order it runs them: as numbered, or longest first.
@@ -333,22 +390,23 @@ struct PlanUse {
 
 // Returns the device-resident work list for H heads with n_masks masks (1: shared,
 // H: one per head), split or not, uploading it on first use on device dev.
-// The forward launch a plan is scheduled for (append_fwd_schedule).
-struct FwdLaunch {
+// The launch a plan is scheduled for: a forward (append_fwd_schedule), or a gradient pass
+// (unit_shares only).
+struct PlanLaunch {
+  bool forward;
   int B, nqb, rows, d, T, P, F, slots_x;
   bool share_tail, by_length;
 };
 
 int work_list_for(const uint8_t* masks, int n_masks, int H, int F, bool allow_split, int dev,
-                  PlanUse* out, const FwdLaunch* fl = nullptr) {
+                  PlanUse* out, const PlanLaunch* fl) {
   std::string key(reinterpret_cast<const char*>(masks), (size_t)n_masks * F * F);
   key += allow_split ? "|s|" : "|u|";
   key += std::to_string(H) + "|" + std::to_string(n_masks) + "|" + std::to_string(F) + "|" +
          std::to_string(dev);
-  if (fl)
-    for (int v : {fl->B, fl->nqb, fl->rows, fl->d, fl->T, fl->P, fl->F, fl->slots_x, (int)fl->share_tail,
-                  (int)fl->by_length})
-      key += "|" + std::to_string(v);
+  for (int v : {(int)fl->forward, fl->B, fl->nqb, fl->rows, fl->d, fl->T, fl->P, fl->F, fl->slots_x,
+                (int)fl->share_tail, (int)fl->by_length})
+    key += "|" + std::to_string(v);
   std::lock_guard<std::mutex> lock(g_cache_mutex);
   if (auto h = g_cache.acquire(key)) {
     out->wl = h->value.wl;
@@ -356,9 +414,11 @@ int work_list_for(const uint8_t* masks, int n_masks, int H, int F, bool allow_sp
     return TA_OK;
   }
   HostWorkList hw = build_work_list(masks, n_masks, H, F, allow_split);
-  if (fl)
+  if (fl->forward)
     append_fwd_schedule(hw, fl->B, fl->nqb, fl->rows, fl->d, fl->T, fl->P, fl->F, fl->slots_x,
                         fl->share_tail, fl->by_length);
+  else
+    unit_shares(hw, fl->B, fl->nqb, fl->rows, fl->T, fl->P, fl->F, hw.share);
   const size_t total = hw.words.size() * sizeof(int32_t);
   void* buf = nullptr;
   hipError_t e = hipMalloc(&buf, total);
@@ -547,6 +607,7 @@ int enqueue_fwd(const void* q, const void* k, const void* v, void* out, int B, i
   a.ws_lse = ws ? ws + frame_rows * d : nullptr;
   a.ws_parts = ws ? ws + frame_rows * (d + 1) : nullptr;
   a.sched = wl->sched_xcd;
+  std::copy(wl->share, wl->share + 9, a.share);
   a.cut_units = wl->cut_units;
   a.n_cut_units = wl->n_cut_units;
   a.wg_per_xcd = wl->wg_per_xcd;
@@ -617,7 +678,7 @@ int run_fwd(const void* q, const void* k, const void* v, void* out, int B, int H
   // The MM-DiT form's units differ much in length (text and global rows keep every
   // segment, other rows a few): each XCD runs its share longest first where that
   // changes the order and the plan splits no frame.
-  const FwdLaunch fl{B, (int)nqb, rows, d, T, P, F, resident_slots_per_xcd(dev), true, P > 0};
+  const PlanLaunch fl{true, B, (int)nqb, rows, d, T, P, F, resident_slots_per_xcd(dev), true, P > 0};
   PlanGuard plan(stream);
   int st = work_list_for(masks, n_masks, H, n_seg, true, dev, &plan.use, &fl);
   if (st != TA_OK) return st;
@@ -627,7 +688,7 @@ int run_fwd(const void* q, const void* k, const void* v, void* out, int B, int H
   };
   if (ws_bytes(plan.use.wl) > kMaxWorkspaceBytes || (int64_t)8 * plan.use.wl.wg_per_xcd > max_wg) {
     end_plan_use(plan.use, stream);
-    const FwdLaunch plain{B, (int)nqb, rows, d, T, P, F, fl.slots_x, false, fl.by_length};
+    const PlanLaunch plain{true, B, (int)nqb, rows, d, T, P, F, fl.slots_x, false, fl.by_length};
     st = work_list_for(masks, n_masks, H, n_seg, false, dev, &plan.use, &plain);  // the same rows, not split
     if (st != TA_OK) return st;
   }
@@ -683,12 +744,14 @@ int run_bwd(const void* q, const void* k, const void* v, const void* out, const 
     masks = aug.data();
   }
   PlanGuard plan_q(stream), plan_k(stream);
-  int st = work_list_for(masks, n_masks, H, n_seg, true, dev, &plan_q.use);
+  const PlanLaunch lq{false, B, (int)nqb, qpw, d, T, P, F, 0, false, false};
+  const PlanLaunch lk{false, B, (int)nkb, kpw, d, T, P, F, 0, false, false};
+  int st = work_list_for(masks, n_masks, H, n_seg, true, dev, &plan_q.use, &lq);
   if (st != TA_OK) return st;
   if ((size_t)plan_q.use.wl.n_slots * part_row > kMaxWorkspaceBytes ||
       (int64_t)B * plan_q.use.wl.n_items * nqb > max_wg) {
     end_plan_use(plan_q.use, stream);
-    st = work_list_for(masks, n_masks, H, n_seg, false, dev, &plan_q.use);
+    st = work_list_for(masks, n_masks, H, n_seg, false, dev, &plan_q.use, &lq);
     if (st != TA_OK) return st;
   }
   const DeviceWorkList* wq = &plan_q.use.wl;
@@ -697,12 +760,12 @@ int run_bwd(const void* q, const void* k, const void* v, const void* out, const 
     for (int i = 0; i < n_seg; ++i)
       for (int j = 0; j < n_seg; ++j)
         mt[((size_t)m * n_seg + i) * n_seg + j] = masks[((size_t)m * n_seg + j) * n_seg + i];
-  st = work_list_for(mt.data(), n_masks, H, n_seg, true, dev, &plan_k.use);
+  st = work_list_for(mt.data(), n_masks, H, n_seg, true, dev, &plan_k.use, &lk);
   if (st != TA_OK) return st;
   if ((size_t)plan_k.use.wl.n_slots * 2 * part_row > kMaxWorkspaceBytes ||
       (int64_t)B * plan_k.use.wl.n_items * nkb > max_wg) {
     end_plan_use(plan_k.use, stream);
-    st = work_list_for(mt.data(), n_masks, H, n_seg, false, dev, &plan_k.use);
+    st = work_list_for(mt.data(), n_masks, H, n_seg, false, dev, &plan_k.use, &lk);
     if (st != TA_OK) return st;
   }
   const DeviceWorkList* wk = &plan_k.use.wl;
@@ -770,6 +833,8 @@ int run_bwd(const void* q, const void* k, const void* v, const void* out, const 
   a.scale = scale;
   a.n_wg_q = (uint32_t)((int64_t)B * wq->n_items * nqb);
   a.n_wg_k = (uint32_t)((int64_t)B * wk->n_items * nkb);
+  std::copy(wq->share, wq->share + 9, a.share_q);
+  std::copy(wk->share, wk->share + 9, a.share_k);
   a.slots_per_xcd = resident_slots_per_xcd(dev);
   e = ta::launch_bwd(a, s);
   if (e != hipSuccess) return fail(TA_ERR_HIP, std::string("gradient launch: ") + hipGetErrorString(e));

@@ -776,14 +776,13 @@ __device__ __forceinline__ void fwd_tail_rows(int wave, const FwdItem& it, const
 // a whole unit (slot -1; in a longest-first schedule n_dp_x is 0 and every unit is an
 // entry). sched holds {start_x, n_dp_x, n_tab_x, first entry} per XCD, then the
 // entries. Launches without a table (TABLE false) give XCD x the contiguous units
-// [x q + min(x, r), + q + (x < r)) of the n = q 8 + r units, computed in place, in
-// order, or with the short last blocks of the segments moved to the end of the share
-// (short_last_unit).
+// [share[x], share[x + 1]), in order, or with the short last blocks of the segments moved
+// to the end of the share (short_last_in_share).
 template <int D, bool PREFIX, bool TABLE>
 __device__ __forceinline__ void fwd_unit(
     int wave, uint32_t x, int pos, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, uint16_t* __restrict__ O, const int32_t* __restrict__ items,
-    const int32_t* __restrict__ cols, int n_items, int B, int H, int F, int T, int P, int nqb,
+    const int32_t* __restrict__ cols, uint32_t share0, uint32_t share1, int n_items, int B, int H, int F, int T, int P, int nqb,
     const int32_t* __restrict__ sched, float* __restrict__ ws_o, float* __restrict__ ws_lse,
     float* __restrict__ lse, float* __restrict__ ws_parts, float c, uint32_t qflip, uint32_t qmask,
     uint16_t (&sK)[2][Shape<D>::kTileElems], uint16_t (&sV)[2][Shape<D>::kTileElems]) {
@@ -795,12 +794,11 @@ __device__ __forceinline__ void fwd_unit(
   it.part = -1;
   uint32_t u;
   if constexpr (!TABLE) {
-    const uint32_t n = (uint32_t)B * per_b;
-    u = share_start(n, x) + (uint32_t)pos;
+    u = share0 + (uint32_t)pos;
     // Where every segment ends on a short block that runs on two waves (fwd_tail_rows),
-    // the share runs those blocks after its full ones (short_last_unit).
+    // the share runs those blocks after its full ones.
     if constexpr (!PREFIX && (D == 64 || D == 96)) {
-      if (nqb > 1 && T - (nqb - 1) * kBlockQ <= 32) u = short_last_unit(n, (uint32_t)nqb, x, (uint32_t)pos);
+      if (nqb > 1 && T - (nqb - 1) * kBlockQ <= 32) u = short_last_in_share(share0, share1, (uint32_t)nqb, (uint32_t)pos);
     }
   } else {
     const int32_t* xi = sched + 4 * x;
@@ -881,6 +879,7 @@ struct FwdKernelArgs {
   float* lse;
   float* ws_parts;
   int* queue;
+  uint32_t share[9];  // see FwdArgs
   int n_wg;  // the grid size
   int n_items, B, H, F, T, P, nqb;
   float c;
@@ -907,19 +906,16 @@ __global__ __launch_bounds__(kThreads, 2) void tile_attn_fwd_kernel(const FwdKer
   const uint32_t x = blockIdx.x % 8;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // Queue positions of XCD y.
-  auto positions = [](uint32_t y, int B, int n_items, int nqb, const int32_t* sched) {
-    if constexpr (!TABLE) {
-      const uint32_t n = (uint32_t)B * (uint32_t)n_items * (uint32_t)nqb;
-      return (int)(n / 8 + (y < n % 8 ? 1u : 0u));
-    } else {
-      return sched[4 * y + 1] + sched[4 * y + 2];
-    }
+  auto positions = [](uint32_t y, uint32_t share0, uint32_t share1, const int32_t* sched) {
+    if constexpr (!TABLE) return (int)(share1 - share0);
+    else return sched[4 * y + 1] + sched[4 * y + 2];
   };
   if constexpr (!PERSIST) {
     const int pos = (int)(blockIdx.x / 8);
-    if (pos >= positions(x, args.B, args.n_items, args.nqb, args.sched)) return;
+    const uint32_t share0 = args.share[x], share1 = args.share[x + 1];
+    if (pos >= positions(x, share0, share1, args.sched)) return;
     fwd_unit<D, PREFIX, TABLE>(wave, x, pos, args.Q, args.K, args.V, args.O, args.items, args.cols,
-                               args.n_items, args.B, args.H, args.F, args.T, PREFIX ? args.P : 0, args.nqb,
+                               share0, share1, args.n_items, args.B, args.H, args.F, args.T, PREFIX ? args.P : 0, args.nqb,
                                args.sched, args.ws_o, args.ws_lse, args.lse, args.ws_parts, args.c, args.qflip,
                                args.qmask, sK, sV);
   } else {
@@ -946,9 +942,10 @@ __global__ __launch_bounds__(kThreads, 2) void tile_attn_fwd_kernel(const FwdKer
       if (first_thread()) s_pos[round & 1] = atomicAdd(ap->queue + x, 1);
       __syncthreads();
       const int pos = __builtin_amdgcn_readfirstlane(s_pos[round & 1]);
-      if (pos >= positions(x, ap->B, ap->n_items, ap->nqb, ap->sched)) break;
+      const uint32_t share0 = ap->share[x], share1 = ap->share[x + 1];
+      if (pos >= positions(x, share0, share1, ap->sched)) break;
       fwd_unit<D, PREFIX, TABLE>(wave, x, pos, ap->Q, ap->K, ap->V, ap->O, ap->items, ap->cols,
-                                 ap->n_items, ap->B, ap->H, ap->F, ap->T, PREFIX ? ap->P : 0, ap->nqb,
+                                 share0, share1, ap->n_items, ap->B, ap->H, ap->F, ap->T, PREFIX ? ap->P : 0, ap->nqb,
                                  ap->sched, ap->ws_o, ap->ws_lse, ap->lse, ap->ws_parts, ap->c, ap->qflip,
                                  ap->qmask, sK, sV);
     }
@@ -1077,10 +1074,11 @@ hipError_t launch_d(const FwdArgs& a, hipStream_t stream) {
   const dim3 grid(8u * (uint32_t)(persist ? std::min(a.wg_per_xcd, a.slots_per_xcd) : a.wg_per_xcd));
   auto go = [&](auto prefix, auto table_c) {
     constexpr bool kPrefix = decltype(prefix)::value, kTable = decltype(table_c)::value;
-    const FwdKernelArgs ka{a.q,      a.k,   a.v,        a.out,   a.items,         a.cols,
-                           a.sched,  a.ws_o, a.ws_lse,  a.lse,   a.ws_parts,      a.queue,
-                           (int)grid.x, a.n_items, a.B, a.H,    a.F,             a.T,
-                           kPrefix ? a.P : 0, nqb, a.c, a.qflip, a.qmask};
+    FwdKernelArgs ka{a.q,      a.k,   a.v,        a.out,   a.items,         a.cols,
+                     a.sched,  a.ws_o, a.ws_lse,  a.lse,   a.ws_parts,      a.queue,
+                     {},       (int)grid.x, a.n_items, a.B, a.H,            a.F,
+                     a.T,      kPrefix ? a.P : 0, nqb, a.c, a.qflip,        a.qmask};
+    std::copy(a.share, a.share + 9, ka.share);
     if (kPrefix && D == 64 && persist)
       hipLaunchKernelGGL((tile_attn_fwd_kernel<D, kPrefix, kTable, kPrefix && D == 64>), grid, dim3(kThreads), 0,
                          stream, ka);

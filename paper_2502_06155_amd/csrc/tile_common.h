@@ -24,13 +24,6 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 
 constexpr int kBlockK = 64;  // tokens per K/V (or Q/dO) tile staged in LDS
 
-// Workgroup id -> logical work index such that the ids the hardware sends to
-// XCD x (those with id % 8 == x) cover one contiguous logical range.
-__device__ __forceinline__ uint32_t xcd_remap(uint32_t id, uint32_t n) {
-  const uint32_t q = n / 8, r = n % 8, x = id % 8, pos = id / 8;
-  return x * q + (x < r ? x : r) + pos;
-}
-
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }

@@ -1,0 +1,76 @@
+// Host-only check of unit_shares (paper_2502_06155_amd/csrc/tile_attn_host.cpp), linked
+// against the built library and run by tests/test_shares.py: the eight shares cover the
+// units in order; a launch whose counts are even to within 3% of the work keeps the equal
+// counts; any other gets shares within one unit of an eighth of the work. Prints "<name>
+// equal 0|1 most M" with M the largest share's work over an eighth of all.
+#include <algorithm>
+#include <cstdio>
+#include <vector>
+
+#include "host_internal.h"
+#include "tile_attn.h"
+#include "unit_order.h"
+
+using namespace ta::host;
+
+// Heads cycle through the (g, form) pairs given.
+static int check(const char* name, int B, int H, int F, int T, int P, int rows,
+                 std::vector<std::pair<int, int>> kinds) {
+  const int n_seg = F + (P > 0);
+  std::vector<uint8_t> masks;
+  for (int h = 0; h < H; ++h) {
+    std::vector<uint8_t> m((size_t)F * F);
+    tile_attn_make_mask(F, kinds[h % kinds.size()].first, kinds[h % kinds.size()].second, m.data());
+    for (int i = 0; i < n_seg; ++i)
+      for (int j = 0; j < n_seg; ++j) masks.push_back(i < F && j < F ? m[(size_t)i * F + j] : 1);
+  }
+  const HostWorkList hw = build_work_list(masks.data(), H, H, n_seg, true);
+  const int nblk = (std::max(T, P) + rows - 1) / rows;
+  uint32_t share[9];
+  unit_shares(hw, B, nblk, rows, T, P, F, share);
+  const uint32_t per_b = (uint32_t)hw.n_items * nblk, n = B * per_b;
+  const int32_t *items = hw.words.data(), *cols = items + hw.off_cols;
+  auto work = [&](uint32_t u) -> double {
+    const int32_t* it = items + 5 * ((u % per_b) / nblk);
+    const int left = (P > 0 && it[1] == F ? P : T) - (int)(u % nblk) * rows;
+    double t = it[3] * ((T + 63) / 64);
+    if (P > 0 && it[3] > 0 && cols[it[2] + it[3] - 1] == F) t += (P + 63) / 64 - (T + 63) / 64;
+    return left <= 0 ? 0 : left <= 32 ? t / 2 + 1 : t + 2;
+  };
+  double total = 0, longest = 0, most = 0, most_equal = 0;
+  for (uint32_t u = 0; u < n; ++u) {
+    total += work(u);
+    longest = std::max(longest, work(u));
+  }
+  bool equal = true;
+  if (share[0] != 0 || share[8] != n) return std::printf("%s: ends\n", name), 1;
+  for (int x = 0; x < 8; ++x) {
+    if (share[x] > share[x + 1]) return std::printf("%s: order\n", name), 1;
+    equal = equal && share[x] == ta::share_start(n, x);
+    double w = 0, we = 0;
+    for (uint32_t u = share[x]; u < share[x + 1]; ++u) w += work(u);
+    for (uint32_t u = ta::share_start(n, x); u < ta::share_start(n, x + 1); ++u) we += work(u);
+    most = std::max(most, w);
+    most_equal = std::max(most_equal, we);
+  }
+  const double even = total / 8;
+  if (most_equal <= 1.0299 * even && !equal) return std::printf("%s: even counts not kept\n", name), 1;
+  if (most_equal > 1.0301 * even && most > even + longest + 8) return std::printf("%s: share of %.3f\n", name, most / even), 1;
+  std::printf("%s equal %d most %.3f\n", name, (int)equal, most / even);
+  return 0;
+}
+
+int main() {
+  const std::pair<int, int> col1{1, TA_MASK_COL}, sym1{1, TA_MASK_SYM}, sym2{2, TA_MASK_SYM}, col4{4, TA_MASK_COL};
+  int bad = 0;
+  bad |= check("uniform", 1, 24, 24, 3600, 0, 256, {col1});
+  bad |= check("mixed-fwd", 1, 6, 24, 3600, 0, 256, {sym2, sym1, col4});
+  bad |= check("mixed-bwd", 1, 6, 24, 3600, 0, 128, {sym2, sym1, col4});
+  bad |= check("mixed-batch", 3, 5, 24, 333, 0, 128, {sym2, sym1, col4});
+  bad |= check("share-sym", 1, 6, 24, 3600, 0, 256, {sym1});
+  bad |= check("mmdit", 1, 5, 13, 1350, 226, 256, {sym2, col1});
+  bad |= check("mmdit-long-text", 2, 3, 7, 40, 300, 128, {sym1, col1});
+  bad |= check("one-unit", 1, 1, 1, 7, 0, 256, {col1});
+  bad |= check("few", 1, 3, 2, 300, 0, 256, {col1});
+  return bad;
+}
