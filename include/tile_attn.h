@@ -36,8 +36,11 @@
  *     parts; a gradient call holds two: the mask's and its transpose's; a forward
  *     plan is cached per launch shape). Beyond that the least recently
  *     used one is evicted; its memory is freed only once no call holds it and
- *     events recorded after every call that used it have completed, so evicting
- *     never waits for a stream. A plan used while its stream is being captured
+ *     an event recorded on each stream after its last use there has completed,
+ *     so evicting does not wait for a stream. (Events are recorded after every
+ *     call that plans and every 16th other one on a stream; if over 64 evicted
+ *     plans hang on a stream that has made no such call since, the next eviction
+ *     waits for the device instead.) A plan used while its stream is being captured
  *     into a graph is never evicted (the graph may replay at any later time). A
  *     mask whose plan splits heavy query frames also needs a workspace for the
  *     partial results, n_slots * B * max(T, P) * (d + 1) * 4 bytes (n_slots
@@ -289,8 +292,8 @@ int tile_attn_fwd_heads_noalloc(const void* q, const void* k, const void* v, voi
 /*
  * Occupancy of the plan cache (all devices): *live receives the number of cached
  * plans (at most TA_PLAN_CACHE_ENTRIES, plus any held by calls in progress or pinned
- * by graph capture), *retired the number of evicted plans whose memory waits for
- * their last kernels to finish. Frees the retired plans whose work is done first.
+ * by graph capture), *retired the number of evicted plans whose memory waits for an
+ * event after their last kernels. Frees the retired plans whose work is done first.
  * Host only; TA_ERR_NULL_PTR for a NULL argument.
  */
 int tile_attn_plan_cache_stats(int* live, int* retired);

@@ -58,3 +58,63 @@ def test_many_masks_stay_within_the_cache_and_evicted_plans_still_work():
     ta.tile_attn_fwd(q, k, v, out1, B, H, F, T, d, first, scale, s)
     torch.cuda.synchronize()
     assert np.array_equal(from_dev(out1), ref0)
+
+
+def test_plans_last_used_on_a_quiet_stream_are_freed():
+    # Cache hits record an event only every 16th time, so the last plans used on a stream
+    # that then goes quiet stay retired; another call there, or enough of them, frees them.
+    B, H, F, T, d = 1, 1, 7, 20, 64
+    qb, kb, vb = workloads.make_qkv(B, H, F, T, d, seed=150)
+    q, k, v = (to_dev(x) for x in (qb, kb, vb))
+    scale = d ** -0.5
+    main, side = torch.cuda.current_stream(), torch.cuda.Stream()
+    side.wait_stream(main)
+    rng = np.random.default_rng(151)
+
+    def masks(n):
+        out = {}
+        while len(out) < n:
+            m = (rng.random((F, F)) < 0.5).astype(np.uint8)
+            out[m.tobytes()] = m
+        return list(out.values())
+
+    def call(m, s):
+        o = torch.empty_like(q)
+        o.record_stream(s)
+        ta.tile_attn_fwd(q, k, v, o, B, H, F, T, d, m, scale, s)
+        return o
+
+    def fill(s):  # CAP new masks: evicts every plan the cache holds
+        for m in masks(CAP):
+            call(m, s)
+
+    fill(main)
+    few = masks(8)
+    for m in few:
+        call(m, side)  # planned: each followed by an event
+    for m in few:
+        call(m, side)  # hits: none
+    fill(main)
+    torch.cuda.synchronize()
+    live, retired = ta.tile_attn_plan_cache_stats()
+    print(f"[cache] quiet stream: live {live} retired {retired}", flush=True)
+    assert live == CAP and retired <= 8
+    o = call(few[0], side)  # plans again: an event covers the side stream's earlier uses
+    torch.cuda.synchronize()
+    live, retired = ta.tile_attn_plan_cache_stats()
+    assert live == CAP and retired == 0
+    assert_parity(from_dev(o), oa.attention(qb, kb, vb, few[0], T, scale), "cache-quiet")
+    # many plans hanging on quiet streams: never more than 64 and one eviction's worth
+    streams = [torch.cuda.Stream() for _ in range(10)]
+    many = masks(80)
+    for m in many:
+        call(m, main)
+    for i, m in enumerate(many):  # eight uncovered uses on each of ten streams
+        streams[i // 8].wait_stream(main)
+        call(m, streams[i // 8])
+    fill(main)
+    fill(main)
+    torch.cuda.synchronize()
+    live, retired = ta.tile_attn_plan_cache_stats()
+    print(f"[cache] quiet streams: live {live} retired {retired}", flush=True)
+    assert live == CAP and retired <= 65
