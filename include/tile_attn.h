@@ -33,13 +33,14 @@
  *     copies of plans are cached, at most TA_PLAN_CACHE_ENTRIES of them (each
  *     4 * (5 * items + kept entries + 4 * split frames) bytes, plus for a forward
  *     launch's schedule 128 bytes, 16 per part and 12 per query block cut into
- *     parts; a gradient call holds two: the mask's and its transpose's; a forward
+ *     parts; a gradient call holds two: the mask's and its transpose's; a
  *     plan is cached per launch shape). Beyond that the least recently
  *     used one is evicted; its memory is freed only once no call holds it and
- *     an event recorded on each stream after its last use there has completed,
- *     so evicting does not wait for a stream. (Events are recorded after every
- *     call that plans and every 16th other one on a stream; if over 64 evicted
- *     plans hang on a stream that has made no such call since, the next eviction
+ *     an event recorded on each stream after its last use there has completed
+ *     or that stream is found idle, so evicting does not wait for a stream. (Events
+ *     are recorded after every call that plans and every 16th other one on a
+ *     stream; if over 64 evicted plans were last used without one on streams
+ *     that are busy or no longer there, the next eviction
  *     waits for the device instead.) A plan used while its stream is being captured
  *     into a graph is never evicted (the graph may replay at any later time). A
  *     mask whose plan splits heavy query frames also needs a workspace for the

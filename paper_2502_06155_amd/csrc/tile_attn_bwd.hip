@@ -23,7 +23,9 @@
 //         the frames that keep it (the work list of the transposed mask):
 //         S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS. Each lane owns
 //         one key of its wave's 32-key column block.
+//         At d = 128 large calls run it with one wave per SIMD (dkdv_roll_unit).
 //   sum   adds the fp32 partials of frames the work plan split into pieces.
+// Small calls run dq and dk/dv in one launch (bwd_all_kernel).
 // dq is recomputed in its own pass instead of being accumulated from the key side:
 // fp32 atomics from every (key block, query block) pair would move several TB/s
 // through L2 at this shape, more than recomputing S and dP costs on the matrix cores.
@@ -609,7 +611,7 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, int nkb, uint32_t wo
         // MFMA i is read from LDS at packet i - 2 into one of three rotating
         // registers (i - 1 and two registers in the dK pass of d = 128), so no MFMA
         // waits on a read issued just before it (3.5% faster than leaving the order to
-        // the compiler). Stream: S (and dP) of half 0, S
+        // the compiler, measured at the 93-frame shape). Stream: S (and dP) of half 0, S
         // (and dP) of half 1 with half 0's P (and dS) forming, the dV/dK update of
         // half 0 with half 1's P (and dS) forming, the update of half 1. The passes of
         // d = 128 run the same stream: the dV pass (S, P, dV) without dP, dS and dK,
@@ -675,7 +677,7 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, int nkb, uint32_t wo
         };
         // Vector work of packet i: LDS reads of -delta (dP starts) and lse2 ahead of
         // their use, and P (and dS) of half 0 over the second half's S/dP packets, of
-        // half 1 over half 0's update packets, 2 queries at a time.
+        // half 1 over half 0's update packets.
         auto side = [&](auto ic) {
           constexpr int i = decltype(ic)::value;
           if constexpr (kWantDk && (i == 0 || i == kHalf)) dp_start(buf, i / kHalf, dp[i / kHalf]);

@@ -365,10 +365,26 @@ struct StreamClock {
   struct Mark { uint64_t number; hipEvent_t event; };
   std::vector<Mark> marks;          // recorded, oldest first
   std::vector<hipEvent_t> spare;    // finished events, to record again
+  int dev = 0;
+  hipStream_t stream = nullptr;
+  std::thread::id thread;           // of hipStreamPerThread's clocks, else none
+  // Every use so far is known complete if the stream is idle now. Asked only about uses no
+  // event covers (the last few on a stream that then went quiet), never of a stream that
+  // is being captured, nor of another device's or thread's.
+  void poll_stream() {
+    int cur = 0;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipGetDevice(&cur) == hipSuccess && cur == dev &&
+        (thread == std::thread::id() || thread == std::this_thread::get_id()) &&
+        hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
+        hipStreamQuery(stream) == hipSuccess)
+      done = recorded = uses;
+    (void)hipGetLastError();
+  }
   void poll() {
     size_t n = 0;
     while (n < marks.size() && hipEventQuery(marks[n].event) == hipSuccess) {
-      done = marks[n].number;
+      done = std::max(done, marks[n].number);
       spare.push_back(marks[n++].event);
     }
     marks.erase(marks.begin(), marks.begin() + n);
@@ -400,8 +416,8 @@ struct StreamClock {
   static constexpr size_t kMaxMarks = 4;
 };
 constexpr uint64_t kUsesPerMark = 16;
-// Evicted plans whose last use no event covers (their stream made no further call since):
-// beyond this many, the next eviction waits for the device and frees them.
+// Evicted plans whose last use no event covers and whose stream cannot be asked (destroyed,
+// or another thread's): beyond this many, the next eviction waits for the device instead.
 constexpr int kMaxUncovered = 64;
 
 // Clocks by device and stream; hipStreamPerThread is another stream in every thread.
@@ -409,7 +425,12 @@ std::map<std::pair<std::pair<int, void*>, std::thread::id>, StreamClock> g_clock
 
 StreamClock* clock_of(int dev, void* stream) {
   const bool per_thread = stream == (void*)hipStreamPerThread;
-  return &g_clocks[{{dev, stream}, per_thread ? std::this_thread::get_id() : std::thread::id()}];
+  const std::thread::id thread = per_thread ? std::this_thread::get_id() : std::thread::id();
+  StreamClock& c = g_clocks[{{dev, stream}, thread}];
+  c.dev = dev;
+  c.stream = static_cast<hipStream_t>(stream);
+  c.thread = thread;
+  return &c;
 }
 
 // A cached plan: its device buffer and, per stream that enqueued work with it, the number
@@ -421,11 +442,12 @@ struct CachedPlan {
 };
 
 struct HipPlanOps {
-  int uncovered = 0;  // plans found waiting for an event nobody recorded
+  int uncovered = 0;  // plans found with a use that no event covers
   bool idle(CachedPlan& p) {
     bool done = true, covered = true;
     for (auto& u : p.uses) {
       if (u.first->done < u.second) u.first->poll();
+      if (u.first->recorded < u.second) u.first->poll_stream();
       done = done && u.first->done >= u.second;
       covered = covered && u.first->recorded >= u.second;
     }
