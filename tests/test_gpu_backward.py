@@ -471,3 +471,35 @@ def test_bwd_launch_per_pass_matches_one_launch_bitwise(d, P):
         for x, y in zip(whole, one):
             assert bool(torch.isfinite(x[b].float()).all())
             assert torch.equal(x[b], y)
+
+
+@pytest.mark.parametrize("scale", [128 ** -0.5, -0.1, 0.0])
+@pytest.mark.parametrize("T", [1, 31, 32, 33, 64, 65, 129])
+def test_bwd_d128_one_wave_per_simd_matches_two_passes_bitwise(T, scale):
+    # 64 heads are 3.75 rounds of workgroups and more (dK and dV in one pass, one wave per
+    # SIMD), eight of them at most one (two passes in the shared launch). Both add the same
+    # products in the same order, 16 queries at a time. Blocks of 32 queries and their
+    # remainders, key frames that nobody keeps, query frames that keep nothing, and a heavy
+    # row and column, which are split into partials.
+    B, H, F, d = 1, 64, 10, 128
+    rng = np.random.default_rng(T)
+    masks = (rng.random((H, F, F)) < 0.15).astype(np.uint8)
+    masks[:, 4, :], masks[:, :, 7] = 1, 1
+    masks[::3, 2, :], masks[::3, :, 5] = 0, 0
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    q, k, v, g = (torch.randn((B, H, F * T, d), generator=gen, device="cuda").to(torch.bfloat16)
+                  for _ in range(4))
+    s = torch.cuda.current_stream()
+    out = torch.empty_like(q)
+    lse = torch.empty((B, H, F * T), dtype=torch.float32, device="cuda")
+    ta.tile_attn_fwd_heads(q, k, v, out, B, H, F, T, d, masks, scale, lse, s)
+    whole = [torch.full_like(q, float("nan")) for _ in range(3)]
+    ta.tile_attn_bwd(q, k, v, out, g, lse, *whole, B, H, F, T, d, masks, scale, s)
+    print(f"[case] bwd d128 T={T} scale={scale}", flush=True)
+    for h in range(0, H, 8):
+        part = [x[:, h:h + 8].contiguous() for x in (q, k, v, out, g, lse)]
+        some = [torch.full_like(part[0], float("nan")) for _ in range(3)]
+        ta.tile_attn_bwd(*part, *some, B, 8, F, T, d, masks[h:h + 8], scale, s)
+        for x, y in zip(whole, some):
+            assert bool(torch.isfinite(y.float()).all())
+            assert torch.equal(x[:, h:h + 8], y)
