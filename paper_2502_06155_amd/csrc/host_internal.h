@@ -55,8 +55,10 @@ int resident_slots_per_xcd(int dev);
 
 // Deals the units (b, item, block of `rows` rows; nblk blocks per segment) of hw out to the
 // eight XCDs as contiguous shares: XCD x gets [share[x], share[x + 1]). By count where that
-// is even to within 3% of the work, else by work (kept 64-token tiles, half for a block of
-// at most 32 rows, which takes about half a full block's time).
+// is even to within 3% of the work or the launch holds fewer than kMinUnitsByWork units
+// (two rounds of resident workgroups), else by work (kept 64-token tiles, half for a block
+// of at most 32 rows, which takes about half a full block's time).
+constexpr int64_t kMinUnitsByWork = 2 * 8 * 64;
 void unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, uint32_t share[9]);
 
 // Appends the forward launch schedule to hw (see FwdArgs::sched): B batch entries, nqb

@@ -147,7 +147,9 @@ HostWorkList build_work_list(const uint8_t* masks, int n_masks, int H, int F, bo
 // (by count -> by work, same process): H = 6, 24 x 3600 at d = 96, one mask per head (sym
 // g = 2, sym g = 1, col g = 4) forward 3.435 -> 2.534 ms, gradients 9.71 -> 8.56 ms; sym g = 1
 // for all heads 1.867 -> 1.819 and 6.23 -> 5.98 ms. Launches whose counts are even (every
-// multiple of 8 heads under one mask) keep them, to the unit. Ordering each share longest
+// multiple of 8 heads under one mask) keep them, to the unit. So do launches of under two
+// rounds, where the counts decide how many units share a compute unit (H = 15, 43 x 60 at
+// d = 96, one mask per head: 49.5 us by count, 52.1 by work). Ordering each share longest
 // first as well gained nothing where it mattered (2.65 ms).
 void unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, uint32_t share[9]) {
   const int32_t* items = hw.words.data();
@@ -180,7 +182,7 @@ void unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P
     for (int64_t blk = 0; blk < u % nblk; ++blk) w += unit2(i, blk);
     return w;
   };
-  if (n == 0 || total == 0) return;
+  if (n < kMinUnitsByWork || total == 0) return;
   int64_t most = 0;
   for (int x = 0; x < 8; ++x) most = std::max(most, work_before(share[x + 1]) - work_before(share[x]));
   if (most * 800 <= B * total * 103) return;  // most <= 1.03 * (B total / 8)

@@ -1,7 +1,7 @@
 // Host-only check of unit_shares (paper_2502_06155_amd/csrc/tile_attn_host.cpp), linked
 // against the built library and run by tests/test_shares.py: the eight shares cover the
-// units in order; a launch whose counts are even to within 3% of the work keeps the equal
-// counts; any other gets shares within one unit of an eighth of the work. Prints "<name>
+// units in order; a launch of few units, or whose counts are even to within 3% of the work,
+// keeps the equal counts; any other gets shares within one unit of an eighth of the work. Prints "<name>
 // equal 0|1 most M" with M the largest share's work over an eighth of all.
 #include <algorithm>
 #include <cstdio>
@@ -54,8 +54,9 @@ static int check(const char* name, int B, int H, int F, int T, int P, int rows,
     most_equal = std::max(most_equal, we);
   }
   const double even = total / 8;
+  if (n < kMinUnitsByWork && !equal) return std::printf("%s: few units not by count\n", name), 1;
   if (most_equal <= 1.0299 * even && !equal) return std::printf("%s: even counts not kept\n", name), 1;
-  if (most_equal > 1.0301 * even && most > even + longest + 8) return std::printf("%s: share of %.3f\n", name, most / even), 1;
+  if (n >= kMinUnitsByWork && most_equal > 1.0301 * even && most > even + longest + 8) return std::printf("%s: share of %.3f\n", name, most / even), 1;
   std::printf("%s equal %d most %.3f\n", name, (int)equal, most / even);
   return 0;
 }
