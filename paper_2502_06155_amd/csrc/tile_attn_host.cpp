@@ -250,13 +250,19 @@ void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int 
   // or 96), the kernel runs those blocks on two waves, after the full blocks of each
   // XCD's share, and they already even out the last round: no parts then.
   const bool short_last = P == 0 && (d == 64 || d == 96) && nqb > 1 && T - (nqb - 1) * rows <= 32;
+  // Where a ragged round may be cut into parts, the shares stay by count: they decide which
+  // units are cut and into how many parts, so a plan's rounding would change with them.
+  const bool may_cut = share_tail && hw.n_heavy == 0 && !short_last;
   std::vector<int32_t> xcd(4 * 8), pieces, cut_units;
   int n_part_slots = 0;
   int64_t wg_max = 0;
   // Longest first where it changes something: a plan with split frames runs the
   // kernel's persistent loop instead (its queue takes the natural order), and a share
   // whose units with rows already come longest first keeps the contiguous form.
-  unit_shares(hw, B, nqb, rows, T, P, F, hw.share);
+  if (may_cut)
+    for (uint32_t x = 0; x <= 8; ++x) hw.share[x] = ta::share_start((uint32_t)n, x);
+  else
+    unit_shares(hw, B, nqb, rows, T, P, F, hw.share);
   bool table = false;
   if (by_length && hw.n_heavy == 0) {
     for (int x = 0; x < 8 && !table; ++x) {
@@ -292,7 +298,7 @@ void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int 
     // even out the last round, and parts of pieces would add a second merge.
     const int64_t ragged = cnt % slots_x;
     int parts_k = 1;
-    if (share_tail && hw.n_heavy == 0 && !short_last && cnt > slots_x && ragged > 0) {
+    if (may_cut && cnt > slots_x && ragged > 0) {
       double mean_tiles = 0;
       for (int64_t i = cnt - ragged; i < cnt; ++i) mean_tiles += (double)unit_tiles(us[i]);
       mean_tiles /= (double)ragged;

@@ -2,7 +2,8 @@
 // against the built library and run by tests/test_shares.py: the eight shares cover the
 // units in order; a launch of few units, or whose counts are even to within 3% of the work,
 // keeps the equal counts; any other gets shares within one unit of an eighth of the work. Prints "<name>
-// equal 0|1 most M" with M the largest share's work over an eighth of all.
+// equal 0|1 most M" with M the largest share's work over an eighth of all. It also checks that
+// append_fwd_schedule keeps the equal counts where it may cut units into parts.
 #include <algorithm>
 #include <cstdio>
 #include <vector>
@@ -61,6 +62,26 @@ static int check(const char* name, int B, int H, int F, int T, int P, int rows,
   return 0;
 }
 
+// A forward launch whose ragged round may be cut into parts keeps the shares by count: they
+// decide which units are cut, and with them how its sums are rounded. Prints "<name> cut U
+// units", U the units cut.
+static int check_cut(const char* name, int B, int H, int F, int T, int d, int g) {
+  const int rows = d == 128 ? 128 : 256, nqb = (T + rows - 1) / rows;
+  std::vector<uint8_t> m((size_t)F * F);
+  tile_attn_make_mask(F, g, TA_MASK_SYM, m.data());
+  HostWorkList hw = build_work_list(m.data(), 1, H, F, true);
+  append_fwd_schedule(hw, B, nqb, rows, d, T, 0, F, 64, true);
+  const uint32_t n = (uint32_t)B * hw.n_items * nqb;
+  const int32_t* xcd = hw.words.data() + hw.off_xcd;
+  if (hw.n_heavy != 0) return std::printf("%s: frames split\n", name), 1;
+  for (int x = 0; x < 8; ++x)
+    if (hw.share[x] != ta::share_start(n, x) || xcd[4 * x] != (int)hw.share[x])
+      return std::printf("%s: shares not by count\n", name), 1;
+  if (hw.share[8] != n) return std::printf("%s: end\n", name), 1;
+  std::printf("%s cut %d units\n", name, hw.n_cut_units);
+  return 0;
+}
+
 int main() {
   const std::pair<int, int> col1{1, TA_MASK_COL}, sym1{1, TA_MASK_SYM}, sym2{2, TA_MASK_SYM}, col4{4, TA_MASK_COL};
   int bad = 0;
@@ -73,5 +94,9 @@ int main() {
   bad |= check("mmdit-long-text", 2, 3, 7, 40, 300, 128, {sym1, col1});
   bad |= check("one-unit", 1, 1, 1, 7, 0, 256, {col1});
   bad |= check("few", 1, 3, 2, 300, 0, 256, {col1});
+  bad |= check_cut("cut-d64", 1, 14, 9, 2883, 64, 5);
+  bad |= check_cut("cut-d96", 1, 18, 24, 555, 96, 8);
+  bad |= check_cut("cut-batch", 2, 3, 25, 2264, 64, 7);
+  bad |= check_cut("cut-d128", 1, 13, 4, 3231, 128, 3);
   return bad;
 }

@@ -33,3 +33,5 @@ def test_shares_hold_equal_work(tmp_path):
     assert got["uniform"][0] == 1
     for name in ("mixed-fwd", "mixed-bwd", "share-sym"):
         assert got[name][0] == 0 and got[name][1] < 1.02, name
+    cut = re.findall(r"^(cut-\S+) cut (\d+) units$", res.stdout, re.M)
+    assert len(cut) == 4 and sum(int(n) for _, n in cut) > 0
