@@ -36,7 +36,7 @@ struct DeviceWorkList {
   const int32_t* cut_units = nullptr;
   int n_cut_units = 0, n_part_slots = 0, wg_per_xcd = 0;
   bool unit_table = false;  // every position is a table entry (no contiguous whole units)
-  uint32_t share[9] = {};   // the XCDs' contiguous shares of the units (unit_shares)
+  uint32_t share[9] = {};   // the XCDs' contiguous shares of the units
 };
 
 // The same plan as host words, before upload: offsets of the parts in words.
@@ -57,9 +57,18 @@ int resident_slots_per_xcd(int dev);
 // eight XCDs as contiguous shares: XCD x gets [share[x], share[x + 1]). By count where that
 // is even to within 3% of the work or the launch holds fewer than kMinUnitsByWork units
 // (two rounds of resident workgroups), else by work (kept 64-token tiles, half for a block
-// of at most 32 rows, which takes about half a full block's time).
+// of at most 32 rows, which takes about half a full block's time). Returns whether by work,
+// and then the largest share's work either way.
 constexpr int64_t kMinUnitsByWork = 2 * 8 * 64;
-void unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, uint32_t share[9]);
+bool unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, uint32_t share[9],
+                 int64_t* most_by_count = nullptr, int64_t* most_by_work = nullptr);
+
+// The shares of a forward that cuts no parts: those of unit_shares where they make the launch
+// shorter (to within half a percent), each XCD running its share in order on `slots`
+// workgroups at a time (with short_last its full blocks first), else by count.
+constexpr int64_t kMaxModelledUnits = 32 * 8 * 64;
+void launch_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, int slots,
+                   bool short_last, uint32_t share[9]);
 
 // Appends the forward launch schedule to hw (see FwdArgs::sched): B batch entries, nqb
 // query blocks of `rows` rows per segment, head dimension d, T tokens per frame and P
@@ -68,7 +77,7 @@ void unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P
 // slots_x resident workgroups) runs that round's units in parts over the kept tiles
 // instead, one workgroup per part, merged by log-sum-exp; otherwise every unit is one
 // workgroup. Where that may happen (share_tail, no frame split, no short-block order) the
-// shares are by count, otherwise those of unit_shares. With by_length, a plan that splits no frame and whose units with rows are
+// shares are by count, otherwise those of launch_shares. With by_length, a plan that splits no frame and whose units with rows are
 // not already longest first in every XCD's share runs each share longest first (table
 // entries for every unit; query blocks past their segment's end are left out).
 void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int T, int P, int F,

@@ -13,6 +13,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <numeric>
@@ -142,6 +143,31 @@ HostWorkList build_work_list(const uint8_t* masks, int n_masks, int H, int F, bo
   return hw;
 }
 
+// Twice the kept 64-token tiles of the units of one launch (b, item, block of `rows` rows;
+// nblk blocks per segment), half for a block of at most 32 rows, none past a segment's end.
+struct UnitWork {
+  const int32_t *items, *cols;
+  int64_t n_items, nblk, per_b, n;
+  int rows, T, P, F;
+  int64_t tpf, ptiles;
+  UnitWork(const HostWorkList& hw, int B, int nblk_, int rows_, int T_, int P_, int F_)
+      : items(hw.words.data()), cols(hw.words.data() + hw.off_cols), n_items(hw.n_items), nblk(nblk_),
+        per_b(n_items * nblk), n(B * per_b), rows(rows_), T(T_), P(P_), F(F_), tpf((T + 63) / 64),
+        ptiles((P + 63) / 64) {}
+  int64_t seg_len(int64_t i) const { return P > 0 && items[5 * i + 1] == F ? P : T; }
+  int64_t item(int64_t i) const {  // one full block of item i
+    const int32_t* it = items + 5 * i;
+    const int beg = it[2], cnt = it[3];
+    int64_t t = cnt * tpf;
+    if (P > 0 && cnt > 0 && cols[beg + cnt - 1] == F) t += ptiles - tpf;
+    return 2 * t + 4;  // and a little for the block itself
+  }
+  int64_t unit(int64_t i, int64_t blk) const {
+    const int64_t left = seg_len(i) - blk * rows;
+    return left <= 0 ? 0 : left <= 32 ? item(i) / 2 : item(i);
+  }
+};
+
 // Why by work: with one mask per head, or fewer heads than XCDs under a sym mask, equal
 // counts hold unequal work and the launch lasts as long as the XCD with the most. Measured
 // (by count -> by work, same process): H = 6, 24 x 3600 at d = 96, one mask per head (sym
@@ -151,52 +177,93 @@ HostWorkList build_work_list(const uint8_t* masks, int n_masks, int H, int F, bo
 // rounds, where the counts decide how many units share a compute unit (H = 15, 43 x 60 at
 // d = 96, one mask per head: 49.5 us by count, 52.1 by work). Ordering each share longest
 // first as well gained nothing where it mattered (2.65 ms).
-void unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, uint32_t share[9]) {
-  const int32_t* items = hw.words.data();
-  const int32_t* cols = hw.words.data() + hw.off_cols;
-  const int64_t n_items = hw.n_items, per_b = n_items * nblk, n = B * per_b;
-  const int64_t tpf = (T + 63) / 64, ptiles = (P + 63) / 64;
+bool unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, uint32_t share[9],
+                 int64_t* most_by_count, int64_t* most_by_work) {
+  const UnitWork uw(hw, B, nblk, rows, T, P, F);
+  const int64_t n_items = uw.n_items, per_b = uw.per_b, n = uw.n;
   for (uint32_t x = 0; x <= 8; ++x) share[x] = ta::share_start((uint32_t)n, x);
-  // Twice the work of item i's full blocks; its last block, and the blocks past its end.
-  auto tiles2 = [&](int64_t i) -> int64_t {
-    const int32_t* it = items + 5 * i;
-    const int beg = it[2], cnt = it[3];
-    int64_t t = cnt * tpf;
-    if (P > 0 && cnt > 0 && cols[beg + cnt - 1] == F) t += ptiles - tpf;
-    return 2 * t + 4;  // and a little for the block itself
-  };
-  auto unit2 = [&](int64_t i, int64_t blk) -> int64_t {
-    const int64_t left = (P > 0 && items[5 * i + 1] == F ? P : T) - blk * rows;
-    return left <= 0 ? 0 : left <= 32 ? tiles2(i) / 2 : tiles2(i);
-  };
   std::vector<int64_t> before((size_t)n_items + 1, 0);  // work of the items before i
   for (int64_t i = 0; i < n_items; ++i) {
-    const int64_t len = P > 0 && items[5 * i + 1] == F ? P : T;
-    const int64_t last = (len - 1) / rows;  // the last block with rows
-    before[i + 1] = before[i] + last * tiles2(i) + unit2(i, last);
+    const int64_t last = (uw.seg_len(i) - 1) / rows;  // the last block with rows
+    before[i + 1] = before[i] + last * uw.item(i) + uw.unit(i, last);
   }
   const int64_t total = before[n_items];
   auto work_before = [&](int64_t u) -> int64_t {
     const int64_t b = u / per_b, i = (u % per_b) / nblk;
     int64_t w = b * total + before[i];
-    for (int64_t blk = 0; blk < u % nblk; ++blk) w += unit2(i, blk);
+    for (int64_t blk = 0; blk < u % nblk; ++blk) w += uw.unit(i, blk);
     return w;
   };
-  if (n < kMinUnitsByWork || total == 0) return;
-  int64_t most = 0;
-  for (int x = 0; x < 8; ++x) most = std::max(most, work_before(share[x + 1]) - work_before(share[x]));
-  if (most * 800 <= B * total * 103) return;  // most <= 1.03 * (B total / 8)
+  auto most_work = [&]() {
+    int64_t most = 0;
+    for (int x = 0; x < 8; ++x) most = std::max(most, work_before(share[x + 1]) - work_before(share[x]));
+    return most;
+  };
+  if (n < kMinUnitsByWork || total == 0) return false;
+  const int64_t most = most_work();
+  if (most * 800 <= B * total * 103) return false;  // most <= 1.03 * (B total / 8)
   for (int x = 1; x < 8; ++x) {
     const int64_t target = B * total / 8 * x, b = target / total, w = target - b * total;
     int64_t i = std::upper_bound(before.begin(), before.end(), w) - before.begin() - 1;
     int64_t u = 0;
-    for (int64_t at = before[i]; i < n_items && u < nblk && at + unit2(i, u) / 2 < w; ++u) at += unit2(i, u);
+    for (int64_t at = before[i]; i < n_items && u < nblk && at + uw.unit(i, u) / 2 < w; ++u) at += uw.unit(i, u);
     share[x] = (uint32_t)std::max<int64_t>(share[x - 1], std::min(n, b * per_b + i * nblk + u));
   }
   uint32_t positions = 0;  // the grid holds 8 times the longest share
   for (int x = 0; x < 8; ++x) positions = std::max(positions, share[x + 1] - share[x]);
-  if ((int64_t)8 * positions * ta::kThreads > (int64_t)UINT32_MAX)
+  if ((int64_t)8 * positions * ta::kThreads > (int64_t)UINT32_MAX) {
     for (uint32_t x = 0; x <= 8; ++x) share[x] = ta::share_start((uint32_t)n, x);
+    return false;
+  }
+  if (most_by_count) *most_by_count = most;
+  if (most_by_work) *most_by_work = most_work();
+  return true;
+}
+
+// The time of the launch's longest XCD in units of UnitWork: each runs its share in order on
+// `slots` workgroups at a time (with short_last the full blocks first).
+int64_t modelled_time(const UnitWork& uw, const uint32_t share[9], int slots, bool short_last) {
+  int64_t longest = 0;
+  std::vector<int64_t> busy;
+  for (int x = 0; x < 8; ++x) {
+    const uint32_t s = share[x], e = share[x + 1];
+    busy.assign(slots, 0);  // a heap of the times at which the slots are free, soonest first
+    for (uint32_t pos = 0; pos < e - s; ++pos) {
+      const uint32_t u = short_last ? ta::short_last_in_share(s, e, (uint32_t)uw.nblk, pos) : s + pos;
+      const uint32_t rem = u % (uint32_t)uw.per_b;
+      const int64_t work = uw.unit(rem / (uint32_t)uw.nblk, rem % (uint32_t)uw.nblk);
+      if (work == 0) continue;
+      std::pop_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+      busy.back() += work;
+      longest = std::max(longest, busy.back());
+      std::push_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+    }
+  }
+  return longest;
+}
+
+// Equal work need not mean equal time: an XCD runs rounds of `slots` workgroups, and a share
+// cut by work can end just past a whole round. So a forward takes the cut by work only where
+// it is the shorter one or ends within half a percent: for certain, where its longest XCD
+// would be even if its longest unit came last (in-order dispatch to the first free slot ends
+// by then), else by the model. Measured (59 shapes of 2 to 13 rounds, by work over by count, one
+// process): where the model says no 0.93 to 1.12, 1.016 on average (H = 29, 9 x 775 at d = 96
+// 401.5 -> 439.6 us); else 0.69 to 1.04, 0.95 on average. The model costs about 25 ns of host
+// time per unit and cut, so launches of more than 32 rounds, where at most a few percent are
+// open, stay by count instead. The gradients, whose passes share a launch or come as two long
+// ones, are shorter by work whatever the model says (51 shapes: 0.67 to 1.03, 0.95 on average).
+void launch_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, int slots,
+                   bool short_last, uint32_t share[9]) {
+  int64_t most_count = 0, most_work = 0, longest = 0;
+  if (!unit_shares(hw, B, nblk, rows, T, P, F, share, &most_count, &most_work)) return;
+  const UnitWork uw(hw, B, nblk, rows, T, P, F);
+  for (int64_t i = 0; i < uw.n_items; ++i) longest = std::max(longest, uw.item(i));
+  if (most_work + slots * longest <= most_count) return;
+  uint32_t count[9];
+  for (uint32_t x = 0; x <= 8; ++x) count[x] = ta::share_start((uint32_t)uw.n, x);
+  if (uw.n > kMaxModelledUnits ||
+      200 * modelled_time(uw, share, slots, short_last) > 201 * modelled_time(uw, count, slots, short_last))
+    std::copy(count, count + 9, share);
 }
 
 DeviceWorkList place_work_list(const HostWorkList& hw, void* buf) {
@@ -262,7 +329,7 @@ void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int 
   if (may_cut)
     for (uint32_t x = 0; x <= 8; ++x) hw.share[x] = ta::share_start((uint32_t)n, x);
   else
-    unit_shares(hw, B, nqb, rows, T, P, F, hw.share);
+    launch_shares(hw, B, nqb, rows, T, P, F, slots_x, short_last, hw.share);
   bool table = false;
   if (by_length && hw.n_heavy == 0) {
     for (int x = 0; x < 8 && !table; ++x) {

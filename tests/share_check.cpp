@@ -1,4 +1,4 @@
-// Host-only check of unit_shares (paper_2502_06155_amd/csrc/tile_attn_host.cpp), linked
+// Host-only check of unit_shares and launch_shares (paper_2502_06155_amd/csrc/tile_attn_host.cpp), linked
 // against the built library and run by tests/test_shares.py: the eight shares cover the
 // units in order; a launch of few units, or whose counts are even to within 3% of the work,
 // keeps the equal counts; any other gets shares within one unit of an eighth of the work. Prints "<name>
@@ -62,6 +62,54 @@ static int check(const char* name, int B, int H, int F, int T, int P, int rows,
   return 0;
 }
 
+// launch_shares takes the equal counts or the cut by work, never one that is over half a percent
+// longer: each XCD's units in order on 64 workgroups, the first that is free taking the next. Prints
+// "<name> counts C work W chosen M", the tiles on the longest XCD.
+static int check_choice(const char* name, int B, int H, int F, int T, int P, int rows, bool short_last,
+                        std::vector<std::pair<int, int>> kinds) {
+  const int n_seg = F + (P > 0);
+  std::vector<uint8_t> masks;
+  for (int h = 0; h < H; ++h) {
+    std::vector<uint8_t> m((size_t)F * F);
+    tile_attn_make_mask(F, kinds[h % kinds.size()].first, kinds[h % kinds.size()].second, m.data());
+    for (int i = 0; i < n_seg; ++i)
+      for (int j = 0; j < n_seg; ++j)
+        masks.push_back(i < F && j < F ? m[(size_t)i * F + j] : 1);
+  }
+  const HostWorkList hw = build_work_list(masks.data(), H, H, n_seg, true);
+  const int nblk = (std::max(T, P) + rows - 1) / rows;
+  const uint32_t per_b = (uint32_t)hw.n_items * nblk, n = B * per_b;
+  const int32_t *items = hw.words.data(), *cols = items + hw.off_cols;
+  auto longest = [&](const uint32_t share[9]) {
+    double end = 0;
+    for (int x = 0; x < 8; ++x) {
+      std::vector<double> slot(64, 0);
+      for (int pass = 0; pass < 2; ++pass)  // the short blocks in a second pass of their own
+        for (uint32_t u = share[x]; u < share[x + 1]; ++u) {
+          const int32_t* it = items + 5 * ((u % per_b) / nblk);
+          const int left = (P > 0 && it[1] == F ? P : T) - (int)(u % nblk) * rows;
+          if (left <= 0 || pass != (int)(short_last && u % nblk == (uint32_t)nblk - 1)) continue;
+          double t = it[3] * ((T + 63) / 64) + 2;
+          if (P > 0 && it[3] > 0 && cols[it[2] + it[3] - 1] == F) t += (P + 63) / 64 - (T + 63) / 64;
+          double& at = *std::min_element(slot.begin(), slot.end());
+          at += left <= 32 ? t / 2 : t;
+          end = std::max(end, at);
+        }
+    }
+    return end;
+  };
+  uint32_t count[9], work[9], chosen[9];
+  for (uint32_t x = 0; x <= 8; ++x) count[x] = ta::share_start(n, x);
+  unit_shares(hw, B, nblk, rows, T, P, F, work);
+  launch_shares(hw, B, nblk, rows, T, P, F, 64, short_last, chosen);
+  if (!std::equal(chosen, chosen + 9, count) && !std::equal(chosen, chosen + 9, work))
+    return std::printf("%s: neither cut\n", name), 1;
+  const double c = longest(count), w = longest(work), m = longest(chosen);
+  if (m > 1.005 * c || (n <= kMaxModelledUnits && m > 1.005 * w)) return std::printf("%s: %.0f of %.0f and %.0f\n", name, m, c, w), 1;
+  std::printf("%s counts %.0f work %.0f chosen %.0f\n", name, c, w, m);
+  return 0;
+}
+
 // A forward launch whose ragged round may be cut into parts keeps the shares by count: they
 // decide which units are cut, and with them how its sums are rounded. Prints "<name> cut U
 // units", U the units cut.
@@ -98,5 +146,13 @@ int main() {
   bad |= check_cut("cut-d96", 1, 18, 24, 555, 96, 8);
   bad |= check_cut("cut-batch", 2, 3, 25, 2264, 64, 7);
   bad |= check_cut("cut-d128", 1, 13, 4, 3231, 128, 3);
+  bad |= check_choice("choice-sym4", 1, 18, 24, 555, 0, 256, false, {{4, TA_MASK_SYM}});
+  bad |= check_choice("choice-fwd", 2, 18, 8, 1056, 0, 256, true, {col1, {1, TA_MASK_COL}, sym2});
+  bad |= check_choice("choice-d128", 1, 36, 15, 482, 0, 128, false, {{6, TA_MASK_COL}, col1, {12, TA_MASK_SYM}});
+  bad |= check_choice("choice-tail", 1, 29, 9, 775, 0, 256, true, {{8, TA_MASK_COL}, col1, {9, TA_MASK_SYM}});
+  bad |= check_choice("choice-share-heads", 1, 6, 24, 3600, 0, 256, true, {sym2, sym1, col4});
+  bad |= check_choice("choice-share-sym", 1, 6, 24, 3600, 0, 256, true, {sym1});
+  bad |= check_choice("choice-mmdit", 1, 27, 15, 1350, 226, 128, false, {sym1});
+  bad |= check_choice("choice-many", 1, 41, 47, 3090, 0, 128, false, {col1, col1, sym2});
   return bad;
 }

@@ -35,3 +35,14 @@ def test_shares_hold_equal_work(tmp_path):
         assert got[name][0] == 0 and got[name][1] < 1.02, name
     cut = re.findall(r"^(cut-\S+) cut (\d+) units$", res.stdout, re.M)
     assert len(cut) == 4 and sum(int(n) for _, n in cut) > 0
+    # the cut by work is taken only where it makes the launch shorter
+    choice = {m.group(1): tuple(float(m.group(i)) for i in (2, 3, 4))
+              for m in re.finditer(r"^(choice-\S+) counts (\S+) work (\S+) chosen (\S+)$", res.stdout, re.M)}
+    assert len(choice) == 8
+    for name in ("choice-sym4", "choice-fwd", "choice-d128", "choice-tail"):
+        counts, work, chosen = choice[name]
+        assert work > counts == chosen, name
+    for name in ("choice-share-heads", "choice-many"):
+        counts, work, chosen = choice[name]
+        assert chosen == work < counts, name
+    assert choice["choice-share-sym"][2] <= choice["choice-share-sym"][0]
