@@ -55,8 +55,8 @@ int resident_slots_per_xcd(int dev);
 
 // Deals the units (b, item, block of `rows` rows; nblk blocks per segment) of hw out to the
 // eight XCDs as contiguous shares: XCD x gets [share[x], share[x + 1]). By count where that
-// is even to within 3% of the work or the launch holds fewer than kMinUnitsByWork units
-// (two rounds of resident workgroups), else by work (kept 64-token tiles, half for a block
+// is even to within 3% of the work or the launch holds fewer than kMinUnitsByWork units with
+// rows (two rounds of resident workgroups), else by work (kept 64-token tiles, half for a block
 // of at most 32 rows, which takes about half a full block's time). Returns whether by work,
 // and then the largest share's work either way.
 constexpr int64_t kMinUnitsByWork = 2 * 8 * 64;

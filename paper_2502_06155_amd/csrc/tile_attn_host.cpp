@@ -175,16 +175,20 @@ struct UnitWork {
 // for all heads 1.867 -> 1.819 and 6.23 -> 5.98 ms. Launches whose counts are even (every
 // multiple of 8 heads under one mask) keep them, to the unit. So do launches of under two
 // rounds, where the counts decide how many units share a compute unit (H = 15, 43 x 60 at
-// d = 96, one mask per head: 49.5 us by count, 52.1 by work). Ordering each share longest
-// first as well gained nothing where it mattered (2.65 ms).
+// d = 96, one mask per head: 49.5 us by count, 52.1 by work); blocks past a segment's end do
+// not count (H = 5, 27 x 90 and 663 text tokens at d = 128, gradients, 0.7 rounds: 133.5 and
+// 143.3 us). Ordering each share longest first as well gained nothing where it mattered
+// (2.65 ms).
 bool unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, uint32_t share[9],
                  int64_t* most_by_count, int64_t* most_by_work) {
   const UnitWork uw(hw, B, nblk, rows, T, P, F);
   const int64_t n_items = uw.n_items, per_b = uw.per_b, n = uw.n;
   for (uint32_t x = 0; x <= 8; ++x) share[x] = ta::share_start((uint32_t)n, x);
   std::vector<int64_t> before((size_t)n_items + 1, 0);  // work of the items before i
+  int64_t with_rows = 0;
   for (int64_t i = 0; i < n_items; ++i) {
     const int64_t last = (uw.seg_len(i) - 1) / rows;  // the last block with rows
+    with_rows += B * (last + 1);
     before[i + 1] = before[i] + last * uw.item(i) + uw.unit(i, last);
   }
   const int64_t total = before[n_items];
@@ -199,7 +203,7 @@ bool unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P
     for (int x = 0; x < 8; ++x) most = std::max(most, work_before(share[x + 1]) - work_before(share[x]));
     return most;
   };
-  if (n < kMinUnitsByWork || total == 0) return false;
+  if (with_rows < kMinUnitsByWork || total == 0) return false;
   const int64_t most = most_work();
   if (most * 800 <= B * total * 103) return false;  // most <= 1.03 * (B total / 8)
   for (int x = 1; x < 8; ++x) {

@@ -1,6 +1,6 @@
 // Host-only check of unit_shares and launch_shares (paper_2502_06155_amd/csrc/tile_attn_host.cpp), linked
 // against the built library and run by tests/test_shares.py: the eight shares cover the
-// units in order; a launch of few units, or whose counts are even to within 3% of the work,
+// units in order; a launch of few units with rows, or whose counts are even to within 3% of the work,
 // keeps the equal counts; any other gets shares within one unit of an eighth of the work. Prints "<name>
 // equal 0|1 most M" with M the largest share's work over an eighth of all. It also checks that
 // append_fwd_schedule keeps the equal counts where it may cut units into parts.
@@ -31,6 +31,9 @@ static int check(const char* name, int B, int H, int F, int T, int P, int rows,
   unit_shares(hw, B, nblk, rows, T, P, F, share);
   const uint32_t per_b = (uint32_t)hw.n_items * nblk, n = B * per_b;
   const int32_t *items = hw.words.data(), *cols = items + hw.off_cols;
+  int64_t with_rows = 0;
+  for (uint32_t u = 0; u < n; ++u)
+    with_rows += (P > 0 && items[5 * ((u % per_b) / nblk) + 1] == F ? P : T) > (int)(u % nblk) * rows;
   auto work = [&](uint32_t u) -> double {
     const int32_t* it = items + 5 * ((u % per_b) / nblk);
     const int left = (P > 0 && it[1] == F ? P : T) - (int)(u % nblk) * rows;
@@ -55,9 +58,9 @@ static int check(const char* name, int B, int H, int F, int T, int P, int rows,
     most_equal = std::max(most_equal, we);
   }
   const double even = total / 8;
-  if (n < kMinUnitsByWork && !equal) return std::printf("%s: few units not by count\n", name), 1;
+  if (with_rows < kMinUnitsByWork && !equal) return std::printf("%s: few units not by count\n", name), 1;
   if (most_equal <= 1.0299 * even && !equal) return std::printf("%s: even counts not kept\n", name), 1;
-  if (n >= kMinUnitsByWork && most_equal > 1.0301 * even && most > even + longest + 8) return std::printf("%s: share of %.3f\n", name, most / even), 1;
+  if (with_rows >= kMinUnitsByWork && most_equal > 1.0301 * even && most > even + longest + 8) return std::printf("%s: share of %.3f\n", name, most / even), 1;
   std::printf("%s equal %d most %.3f\n", name, (int)equal, most / even);
   return 0;
 }
@@ -141,6 +144,7 @@ int main() {
   bad |= check("mmdit", 1, 5, 13, 1350, 226, 256, {sym2, col1});
   bad |= check("mmdit-long-text", 2, 3, 7, 40, 300, 128, {sym1, col1});
   bad |= check("one-unit", 1, 1, 1, 7, 0, 256, {col1});
+  bad |= check("few-with-rows", 1, 5, 27, 90, 663, 128, {{2, TA_MASK_COL}});
   bad |= check("few", 1, 3, 2, 300, 0, 256, {col1});
   bad |= check_cut("cut-d64", 1, 14, 9, 2883, 64, 5);
   bad |= check_cut("cut-d96", 1, 18, 24, 555, 96, 8);

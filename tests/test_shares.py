@@ -29,7 +29,7 @@ def test_shares_hold_equal_work(tmp_path):
     assert res.returncode == 0, res.stdout + res.stderr
     got = {m.group(1): (int(m.group(2)), float(m.group(3)))
            for m in re.finditer(r"^(\S+) equal (\d) most (\S+)$", res.stdout, re.M)}
-    assert len(got) == 9
+    assert len(got) == 10
     assert got["uniform"][0] == 1
     for name in ("mixed-fwd", "mixed-bwd", "share-sym"):
         assert got[name][0] == 0 and got[name][1] < 1.02, name
