@@ -144,7 +144,7 @@ int main() {
   bad |= check("mmdit", 1, 5, 13, 1350, 226, 256, {sym2, col1});
   bad |= check("mmdit-long-text", 2, 3, 7, 40, 300, 128, {sym1, col1});
   bad |= check("one-unit", 1, 1, 1, 7, 0, 256, {col1});
-  bad |= check("few-with-rows", 1, 5, 27, 90, 663, 128, {{2, TA_MASK_COL}});
+  bad |= check("few-with-rows", 1, 5, 27, 90, 663, 128, {sym2});
   bad |= check("few", 1, 3, 2, 300, 0, 256, {col1});
   bad |= check_cut("cut-d64", 1, 14, 9, 2883, 64, 5);
   bad |= check_cut("cut-d96", 1, 18, 24, 555, 96, 8);
