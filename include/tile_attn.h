@@ -33,7 +33,7 @@
  *     copies of plans are cached, at most TA_PLAN_CACHE_ENTRIES of them (each
  *     4 * (5 * items + kept entries + 4 * split frames) bytes, plus for a forward
  *     launch's schedule 128 bytes, 16 per part and 12 per query block cut into
- *     parts; a gradient call holds two: the mask's and its transpose's; a
+ *     parts; a gradient call holds two: the mask's and its transpose's; a forward
  *     plan is cached per launch shape). Beyond that the least recently
  *     used one is evicted; its memory is freed only once no call holds it and
  *     an event recorded on each stream after its last use there has completed

@@ -517,6 +517,13 @@ StreamClock* clock_of(int dev, void* stream) {
 struct CachedPlan {
   DeviceWorkList wl;
   int dev = 0;
+  // Gradient plans: the XCDs' shares for the launch shapes seen last.
+  struct Shares {
+    int B, nblk, T, P, F;
+    uint32_t share[9];
+  };
+  std::vector<Shares> shares;
+  size_t next_shares = 0;  // the one to replace
   std::vector<std::pair<StreamClock*, uint64_t>> uses;
 };
 
@@ -555,37 +562,64 @@ struct PlanUse {
   bool planned = false;  // this call built the plan
 };
 
-// Returns the device-resident work list for H heads with n_masks masks (1: shared,
-// H: one per head), split or not, uploading it on first use on device dev.
-// The launch a plan is scheduled for: a forward (append_fwd_schedule), or a gradient pass
-// (unit_shares only).
+// The launch a plan is scheduled for: a forward (append_fwd_schedule), or a gradient pass. A
+// forward's plan holds its schedule; a gradient's depends on the masks alone and serves every
+// launch shape, with the shares (unit_shares) beside it on the host.
 struct PlanLaunch {
   bool forward;
   int B, nqb, rows, d, T, P, F, slots_x;
   bool share_tail, by_length;
 };
 
+// The shares of launch l of plan p, looked up or computed from the plan's host form.
+template <class HostForm>
+void gradient_shares(CachedPlan& p, const PlanLaunch& l, HostForm&& host_form, uint32_t share[9]) {
+  constexpr size_t kShapesPerPlan = 8;
+  auto it = std::find_if(p.shares.begin(), p.shares.end(), [&](const CachedPlan::Shares& s) {
+    return s.B == l.B && s.nblk == l.nqb && s.T == l.T && s.P == l.P && s.F == l.F;
+  });
+  if (it == p.shares.end()) {
+    CachedPlan::Shares s{l.B, l.nqb, l.T, l.P, l.F, {}};
+    unit_shares(host_form(), l.B, l.nqb, l.rows, l.T, l.P, l.F, s.share);
+    if (p.shares.size() < kShapesPerPlan) {
+      it = p.shares.insert(p.shares.end(), s);
+    } else {
+      it = p.shares.begin() + p.next_shares;
+      *it = s;
+      p.next_shares = (p.next_shares + 1) % kShapesPerPlan;
+    }
+  }
+  std::copy(it->share, it->share + 9, share);
+}
+
+// Returns the device-resident work list for H heads with n_masks masks (1: shared,
+// H: one per head), split or not, uploading it on first use on device dev.
 int work_list_for(const uint8_t* masks, int n_masks, int H, int F, bool allow_split, int dev,
                   PlanUse* out, const PlanLaunch* fl) {
   std::string key(reinterpret_cast<const char*>(masks), (size_t)n_masks * F * F);
   key += allow_split ? "|s|" : "|u|";
   key += std::to_string(H) + "|" + std::to_string(n_masks) + "|" + std::to_string(F) + "|" +
          std::to_string(dev);
-  for (int v : {(int)fl->forward, fl->B, fl->nqb, fl->rows, fl->d, fl->T, fl->P, fl->F, fl->slots_x,
-                (int)fl->share_tail, (int)fl->by_length})
-    key += "|" + std::to_string(v);
+  if (fl->forward)
+    for (int v : {fl->B, fl->nqb, fl->rows, fl->d, fl->T, fl->P, fl->F, fl->slots_x, (int)fl->share_tail,
+                  (int)fl->by_length})
+      key += "|" + std::to_string(v);
   std::lock_guard<std::mutex> lock(g_cache_mutex);
   if (auto h = g_cache.acquire(key)) {
     out->wl = h->value.wl;
     out->slot = h;
+    if (!fl->forward)
+      gradient_shares(h->value, *fl, [&] { return build_work_list(masks, n_masks, H, F, allow_split); },
+                      out->wl.share);
     return TA_OK;
   }
   HostWorkList hw = build_work_list(masks, n_masks, H, F, allow_split);
+  CachedPlan cp;
   if (fl->forward)
     append_fwd_schedule(hw, fl->B, fl->nqb, fl->rows, fl->d, fl->T, fl->P, fl->F, fl->slots_x,
                         fl->share_tail, fl->by_length);
   else
-    unit_shares(hw, fl->B, fl->nqb, fl->rows, fl->T, fl->P, fl->F, hw.share);
+    gradient_shares(cp, *fl, [&]() -> const HostWorkList& { return hw; }, hw.share);
   const size_t total = hw.words.size() * sizeof(int32_t);
   void* buf = nullptr;
   hipError_t e = hipMalloc(&buf, total);
@@ -595,7 +629,6 @@ int work_list_for(const uint8_t* masks, int n_masks, int H, int F, bool allow_sp
     (void)hipFree(buf);
     return fail(TA_ERR_HIP, std::string("hipMemcpy: ") + hipGetErrorString(e));
   }
-  CachedPlan cp;
   cp.wl = place_work_list(hw, buf);
   cp.dev = dev;
   g_cache.ops().uncovered = 0;

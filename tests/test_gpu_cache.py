@@ -6,7 +6,7 @@ import pytest
 
 import workloads
 from oracle import attention as oa
-from tests.gpu_helpers import assert_parity, from_dev, to_dev
+from tests.gpu_helpers import assert_parity, from_dev, to_dev, widen
 
 pytestmark = pytest.mark.gpu
 
@@ -118,3 +118,55 @@ def test_plans_last_used_on_a_quiet_stream_are_freed():
     live, retired = ta.tile_attn_plan_cache_stats()
     print(f"[cache] quiet streams: live {live} retired {retired}", flush=True)
     assert live == CAP and retired == 0
+
+
+def test_gradient_plans_serve_every_launch_shape():
+    # The work plan of a gradient pass depends on the masks alone: once a call has planned them,
+    # calls of other batch sizes, frame lengths and head dims plan and allocate nothing, so they
+    # can be captured without a run of their own. Nine shapes: more than a plan remembers shares
+    # for.
+    H, F = 3, 9
+    rng = np.random.default_rng(160)
+    masks = (rng.random((H, F, F)) < 0.3).astype(np.uint8)
+    masks[0, 4, :], masks[:, :, 2] = 1, 1  # split on both sides
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    shapes = [(2, 150, 128), (1, 150, 128), (2, 97, 96), (1, 64, 64), (1, 33, 96), (2, 1, 64),
+              (1, 130, 128), (1, 65, 64), (2, 96, 96)]
+    calls = []
+    with torch.cuda.stream(s):
+        gen = torch.Generator(device="cuda").manual_seed(161)
+        for B, T, d in shapes:
+            q, k, v, g = (torch.randn((B, H, F * T, d), generator=gen, device="cuda").to(torch.bfloat16)
+                          for _ in range(4))
+            out, lse = torch.empty_like(q), torch.empty((B, H, F * T), dtype=torch.float32, device="cuda")
+            ta.tile_attn_fwd_heads(q, k, v, out, B, H, F, T, d, masks, d ** -0.5, lse, s)
+            grads = [torch.full_like(q, float("nan")) for _ in range(3)]
+            calls.append(((q, k, v, out, g, lse, *grads, B, H, F, T, d, masks, d ** -0.5, s), grads))
+
+        def bwd(i):
+            ta.tile_attn_bwd(*calls[i][0])
+
+        bwd(0)  # the largest: plans and sizes the workspace
+        s.synchronize()
+        before = ta.tile_attn_plan_cache_stats()[0]
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            for i in range(1, len(calls)):
+                bwd(i)
+        assert ta.tile_attn_plan_cache_stats()[0] == before
+        for i in range(1, len(calls)):
+            bwd(i)
+        s.synchronize()
+        eager = [[from_dev(x) for x in c[1]] for c in calls]
+        for rep in range(3):
+            for _, grads in calls[1:]:
+                for x in grads:
+                    x.fill_(float("nan"))
+            s.synchronize()
+            graph.replay()
+            s.synchronize()
+            for (_, grads), want in zip(calls[1:], eager[1:]):
+                for x, w in zip(grads, want):
+                    assert np.array_equal(from_dev(x), w), rep
+    assert all(np.isfinite(widen(w)).all() for e in eager for w in e)
