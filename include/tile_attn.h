@@ -35,15 +35,12 @@
  *     launch's schedule 128 bytes, 16 per part and 12 per query block cut into
  *     parts; a gradient call holds two: the mask's and its transpose's; a forward
  *     plan is cached per launch shape). Beyond that the least recently
- *     used one is evicted; its memory is freed only once no call holds it and
- *     an event recorded on each stream after its last use there has completed
- *     or that stream is found idle, so evicting does not wait for a stream. (Events
- *     are recorded after every call that plans and every 16th other one on a
- *     stream; if over 64 evicted plans were last used without one on streams
- *     that are busy or no longer there, the next eviction
- *     waits for the device instead.) A plan used while its stream is being captured
- *     into a graph is never evicted (the graph may replay at any later time). A
- *     mask whose plan splits heavy query frames also needs a workspace for the
+ *     used one is evicted, and its memory freed once no call holds it: the call that
+ *     plans then waits for the device (as hipFree does by itself), and where it
+ *     cannot, because a stream is being captured, the next one that plans does. Calls
+ *     whose plan is cached wait for nothing and record no event. A plan used while its
+ *     stream is being captured into a graph is never evicted (the graph may replay at
+ *     any later time). A mask whose plan splits heavy query frames also needs a workspace for the
  *     partial results, n_slots * B * max(T, P) * (d + 1) * 4 bytes (n_slots
  *     counts the pieces of all heads), and so does a forward launch whose last
  *     round of workgroups on some XCD would be ragged: where the plan splits no
@@ -293,9 +290,9 @@ int tile_attn_fwd_heads_noalloc(const void* q, const void* k, const void* v, voi
 /*
  * Occupancy of the plan cache (all devices): *live receives the number of cached
  * plans (at most TA_PLAN_CACHE_ENTRIES, plus any held by calls in progress or pinned
- * by graph capture), *retired the number of evicted plans whose memory waits for an
- * event after their last kernels. Frees the retired plans whose work is done first.
- * Host only; TA_ERR_NULL_PTR for a NULL argument.
+ * by graph capture), *retired the number of evicted plans that are not freed yet. Tries
+ * to free those first (see above: this waits for the device if there are any).
+ * Launches nothing; TA_ERR_NULL_PTR for a NULL argument.
  */
 int tile_attn_plan_cache_stats(int* live, int* retired);
 

@@ -171,8 +171,8 @@ def tile_attn_plan(tile_mask):
 
 
 def tile_attn_plan_cache_stats():
-    """(live, retired): cached device plans and evicted ones still waiting for their
-    kernels to finish (tile_attn_plan_cache_stats of the C ABI)."""
+    """(live, retired): cached device plans and evicted ones that are not freed yet
+    (tile_attn_plan_cache_stats of the C ABI; waits for the device if there are any)."""
     live, retired = ctypes.c_int(0), ctypes.c_int(0)
     _check(lib.tile_attn_plan_cache_stats(ctypes.byref(live), ctypes.byref(retired)),
            "tile_attn_plan_cache_stats")

@@ -5,7 +5,7 @@
 // A cached value is in use while a caller holds it between acquire() and
 // release() (the host part of a call: from the cache lookup to the enqueue of its
 // kernels) and while kernels enqueued with it may still run, which the policy
-// tracks (Ops::idle, e.g. events recorded after the launches). Evicting a value
+// knows or waits for (Ops::idle). Evicting a value
 // only moves it to a retired list; collect() frees retired values once no caller
 // holds them and Ops::idle says their work is done. A pinned value (one captured
 // into a graph, which may replay at any later time) is never evicted.
@@ -57,7 +57,7 @@ class PlanCache {
     return &live_.front();
   }
 
-  // The caller is done enqueuing work with h (its completion is the policy's business).
+  // The caller has enqueued its work with h (the end of that work is the policy's business).
   void release(Handle h) {
     if (h && h->holders > 0) --h->holders;
   }

@@ -18,7 +18,6 @@
 #include <mutex>
 #include <numeric>
 #include <string>
-#include <thread>
 #include <utility>
 #include <vector>
 
@@ -430,90 +429,7 @@ void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int 
   hw.unit_table = table;
 }
 
-// How far the work of one stream has got. Every plan use takes the next number of its
-// stream's clock; an event is recorded after a use that planned (it may evict others) and
-// after every kUsesPerMark-th use, not after every call: the event's packet kept the
-// next call's first kernel from starting for 5.6 us (two events in a gradient call, 10.3 us:
-// kernel trace of repeated calls). 2 x 4 heads of 5 x 257 tokens at d = 96, gradients back to
-// back: 38.7 -> 29.4 us; the smallest forward (2 heads of 4 x 64, d = 64), from Python: 13.2
-// -> 10.1 us.
-struct StreamClock {
-  uint64_t uses = 0;      // numbers handed out
-  uint64_t recorded = 0;  // the newest number an event covers
-  uint64_t done = 0;      // the newest number known complete
-  struct Mark { uint64_t number; hipEvent_t event; };
-  std::vector<Mark> marks;          // recorded, oldest first
-  std::vector<hipEvent_t> spare;    // finished events, to record again
-  int dev = 0;
-  hipStream_t stream = nullptr;
-  std::thread::id thread;           // of hipStreamPerThread's clocks, else none
-  // Every use so far is known complete if the stream is idle now. Asked only about uses no
-  // event covers (the last few on a stream that then went quiet), never of a stream that
-  // is being captured, nor of another device's or thread's.
-  void poll_stream() {
-    int cur = 0;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipGetDevice(&cur) == hipSuccess && cur == dev &&
-        (thread == std::thread::id() || thread == std::this_thread::get_id()) &&
-        hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone &&
-        hipStreamQuery(stream) == hipSuccess)
-      done = recorded = uses;
-    (void)hipGetLastError();
-  }
-  void poll() {
-    size_t n = 0;
-    while (n < marks.size() && hipEventQuery(marks[n].event) == hipSuccess) {
-      done = std::max(done, marks[n].number);
-      spare.push_back(marks[n++].event);
-    }
-    marks.erase(marks.begin(), marks.begin() + n);
-    (void)hipGetLastError();  // a pending event's status is not an error of the caller's
-  }
-  // Covers every use so far; false if no event could be recorded. Asks no event's state:
-  // only an eviction and the cache's statistics do (idle).
-  bool mark(hipStream_t s) {
-    if (marks.size() >= kMaxMarks) {  // move the newest event on instead
-      if (hipEventRecord(marks.back().event, s) != hipSuccess) return false;
-      marks.back().number = recorded = uses;
-      return true;
-    }
-    hipEvent_t ev = nullptr;
-    if (!spare.empty()) {
-      ev = spare.back();
-      spare.pop_back();
-    } else if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
-      return false;
-    }
-    if (hipEventRecord(ev, s) != hipSuccess) {
-      spare.push_back(ev);
-      return false;
-    }
-    marks.push_back({uses, ev});
-    recorded = uses;
-    return true;
-  }
-  static constexpr size_t kMaxMarks = 4;
-};
-constexpr uint64_t kUsesPerMark = 16;
-// Evicted plans whose last use no event covers and whose stream cannot be asked (destroyed,
-// or another thread's): beyond this many, the next eviction waits for the device instead.
-constexpr int kMaxUncovered = 64;
-
-// Clocks by device and stream; hipStreamPerThread is another stream in every thread.
-std::map<std::pair<std::pair<int, void*>, std::thread::id>, StreamClock> g_clocks;
-
-StreamClock* clock_of(int dev, void* stream) {
-  const bool per_thread = stream == (void*)hipStreamPerThread;
-  const std::thread::id thread = per_thread ? std::this_thread::get_id() : std::thread::id();
-  StreamClock& c = g_clocks[{{dev, stream}, thread}];
-  c.dev = dev;
-  c.stream = static_cast<hipStream_t>(stream);
-  c.thread = thread;
-  return &c;
-}
-
-// A cached plan: its device buffer and, per stream that enqueued work with it, the number
-// of its last use there.
+// A cached plan and its device.
 struct CachedPlan {
   DeviceWorkList wl;
   int dev = 0;
@@ -524,29 +440,34 @@ struct CachedPlan {
   };
   std::vector<Shares> shares;
   size_t next_shares = 0;  // the one to replace
-  std::vector<std::pair<StreamClock*, uint64_t>> uses;
 };
 
+// An evicted plan is freed after a wait for its device: hipFree is one by its own contract, and
+// once every plan in use is released (after its call has enqueued its kernels) that covers
+// them on all streams. Nothing is asked of a stream handle after the call that passed it, and
+// no event is recorded per call: its packet kept the next call's first kernel from starting
+// for 5.6 us (two events in a gradient call, 10.3 us; kernel trace of repeated calls). 2 x 4
+// heads of 5 x 257 tokens at d = 96, gradients back to back: 38.7 -> 29.4 us; the smallest
+// forward (2 heads of 4 x 64, d = 64), from Python: 13.2 -> 10.1 us.
 struct HipPlanOps {
-  int uncovered = 0;  // plans found with a use that no event covers
-  bool idle(CachedPlan& p) {
-    bool done = true, covered = true;
-    for (auto& u : p.uses) {
-      if (u.first->done < u.second) u.first->poll();
-      if (u.first->recorded < u.second) u.first->poll_stream();
-      done = done && u.first->done >= u.second;
-      covered = covered && u.first->recorded >= u.second;
-    }
-    uncovered += !covered;
-    return done;
-  }
-  void release(CachedPlan& p) {
+  // Runs f with device dev current; clears the error of a call that failed.
+  template <class F>
+  static bool on_device(int dev, F&& f) {
     int cur = 0;
-    const bool restore = hipGetDevice(&cur) == hipSuccess && cur != p.dev;
-    if (restore) (void)hipSetDevice(p.dev);
-    (void)hipFree(p.wl.buffer);
+    const bool restore = hipGetDevice(&cur) == hipSuccess && cur != dev;
+    if (restore) (void)hipSetDevice(dev);
+    const bool ok = f() == hipSuccess;
     if (restore) (void)hipSetDevice(cur);
     (void)hipGetLastError();
+    return ok;
+  }
+  // False where the wait fails (while a stream is being captured): the plan is kept and tried
+  // again when the next call plans.
+  bool idle(CachedPlan& p) {
+    return on_device(p.dev, [] { return hipDeviceSynchronize(); });
+  }
+  void release(CachedPlan& p) {
+    on_device(p.dev, [&] { return hipFree(p.wl.buffer); });
   }
 };
 
@@ -555,11 +476,10 @@ ta::PlanCache<CachedPlan, HipPlanOps> g_cache(TA_PLAN_CACHE_ENTRIES);
 
 // A plan acquired for one call: a copy of its device addresses, and the cache slot the
 // call holds until end_plan_use() (so no eviction frees it before the call's kernels are
-// enqueued and their completion can be tracked).
+// enqueued).
 struct PlanUse {
   DeviceWorkList wl;
   ta::PlanCache<CachedPlan, HipPlanOps>::Handle slot = nullptr;
-  bool planned = false;  // this call built the plan
 };
 
 // The launch a plan is scheduled for: a forward (append_fwd_schedule), or a gradient pass. A
@@ -631,22 +551,15 @@ int work_list_for(const uint8_t* masks, int n_masks, int H, int F, bool allow_sp
   }
   cp.wl = place_work_list(hw, buf);
   cp.dev = dev;
-  g_cache.ops().uncovered = 0;
   auto h = g_cache.insert(std::move(key), std::move(cp));
-  if (g_cache.ops().uncovered > kMaxUncovered && hipDeviceSynchronize() == hipSuccess) {
-    for (auto& c : g_clocks)
-      if (c.first.first.first == dev) c.second.done = c.second.recorded = c.second.uses;
-    g_cache.collect();
-  }
   out->wl = h->value.wl;
   out->slot = h;
-  out->planned = true;
   return TA_OK;
 }
 
-// The call has enqueued every kernel that reads the plan on `stream` (or failed to): number
-// the use on the stream's clock, or, when the stream is being captured into a graph that
-// may replay at any later time, keep the plan for the rest of the process.
+// The call has enqueued every kernel that reads the plan on `stream` (or failed to). Where the
+// stream is being captured into a graph that may replay at any later time, the plan is kept
+// for the rest of the process.
 void end_plan_use(PlanUse& u, void* stream) {
   if (!u.slot) return;
   std::lock_guard<std::mutex> lock(g_cache_mutex);
@@ -655,18 +568,6 @@ void end_plan_use(PlanUse& u, void* stream) {
   if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
     (void)hipGetLastError();
     g_cache.pin(u.slot);
-  } else {
-    StreamClock* clock = clock_of(u.slot->value.dev, stream);
-    const uint64_t number = ++clock->uses;
-    auto& uses = u.slot->value.uses;
-    auto it = std::find_if(uses.begin(), uses.end(),
-                           [&](const std::pair<StreamClock*, uint64_t>& x) { return x.first == clock; });
-    if (it != uses.end()) it->second = number;
-    else uses.emplace_back(clock, number);
-    if ((u.planned || number - clock->recorded >= kUsesPerMark) && !clock->mark(s)) {
-      (void)hipGetLastError();
-      g_cache.pin(u.slot);  // completion cannot be tracked: never free it
-    }
   }
   g_cache.release(u.slot);
   u.slot = nullptr;

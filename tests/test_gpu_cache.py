@@ -1,6 +1,8 @@
 """The bounded plan cache on the GPU: many distinct masks keep it at its capacity, and
 a mask whose plan was evicted (and freed once its kernels finished) is planned again
 and still matches the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -17,6 +19,12 @@ if not torch.cuda.is_available():
 import paper_2502_06155_amd as ta  # noqa: E402
 
 CAP = 256  # TA_PLAN_CACHE_ENTRIES
+
+
+def _hip_library() -> str:
+    """The path of the HIP runtime this process has loaded."""
+    with open("/proc/self/maps") as f:
+        return next(line.split()[-1] for line in f if "libamdhip64.so" in line)
 
 
 def test_many_masks_stay_within_the_cache_and_evicted_plans_still_work():
@@ -61,8 +69,8 @@ def test_many_masks_stay_within_the_cache_and_evicted_plans_still_work():
 
 
 def test_plans_last_used_on_a_quiet_stream_are_freed():
-    # Cache hits record an event only every 16th time, so nothing covers the last uses of
-    # plans on a stream that then goes quiet: they are freed once the stream is idle.
+    # The call that evicts a plan waits for the device and frees it, whichever streams it was
+    # last used on and however long ago.
     B, H, F, T, d = 1, 1, 7, 20, 64
     qb, kb, vb = workloads.make_qkv(B, H, F, T, d, seed=150)
     q, k, v = (to_dev(x) for x in (qb, kb, vb))
@@ -91,9 +99,9 @@ def test_plans_last_used_on_a_quiet_stream_are_freed():
     fill(main)
     few = masks(8)
     for m in few:
-        call(m, side)  # planned: each followed by an event
+        call(m, side)  # planned
     for m in few:
-        call(m, side)  # hits: none
+        call(m, side)  # hits
     fill(main)
     torch.cuda.synchronize()
     live, retired = ta.tile_attn_plan_cache_stats()
@@ -109,7 +117,7 @@ def test_plans_last_used_on_a_quiet_stream_are_freed():
     many = masks(80)
     for m in many:
         call(m, main)
-    for i, m in enumerate(many):  # eight uncovered uses on each of ten streams
+    for i, m in enumerate(many):  # eight hits on each of ten streams
         streams[i // 8].wait_stream(main)
         call(m, streams[i // 8])
     fill(main)
@@ -118,6 +126,43 @@ def test_plans_last_used_on_a_quiet_stream_are_freed():
     live, retired = ta.tile_attn_plan_cache_stats()
     print(f"[cache] quiet streams: live {live} retired {retired}", flush=True)
     assert live == CAP and retired == 0
+
+
+def test_plans_used_on_destroyed_streams_are_freed():
+    # Plans last used on streams that are synchronised and destroyed, whose handles later
+    # streams may receive: eviction asks nothing of a stream, so they are freed as any others.
+    hip = ctypes.CDLL(_hip_library())
+    B, H, F, T, d = 1, 1, 8, 20, 64
+    qb, kb, vb = workloads.make_qkv(B, H, F, T, d, seed=170)
+    q, k, v = (to_dev(x) for x in (qb, kb, vb))
+    scale = d ** -0.5
+    rng = np.random.default_rng(171)
+    torch.cuda.synchronize()
+
+    def call(m, s):
+        o = torch.full_like(q, float("nan"))
+        torch.cuda.synchronize()
+        ta.tile_attn_fwd(q, k, v, o, B, H, F, T, d, m, scale, s)
+        return o
+
+    def on_own_stream(m):
+        s = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(s)) == 0
+        o = call(m, s.value)
+        o = call(m, s.value)  # a hit
+        assert hip.hipStreamSynchronize(s) == 0 and hip.hipStreamDestroy(s) == 0
+        return o
+
+    few = [(rng.random((F, F)) < 0.5).astype(np.uint8) for _ in range(80)]
+    outs = [on_own_stream(m) for m in few]
+    for _ in range(CAP):
+        call((rng.random((F, F)) < 0.5).astype(np.uint8), torch.cuda.current_stream())
+    assert ta.tile_attn_plan_cache_stats() == (CAP, 0)
+    again = on_own_stream(few[0])  # planned again, on a handle that may have been used before
+    torch.cuda.synchronize()
+    assert np.array_equal(from_dev(again), from_dev(outs[0]))
+    for m, o in zip(few[::16], outs[::16]):
+        assert_parity(from_dev(o), oa.attention(qb, kb, vb, m, T, scale), "cache-destroyed-stream")
 
 
 def test_gradient_plans_serve_every_launch_shape():
