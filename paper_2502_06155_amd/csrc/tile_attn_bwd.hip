@@ -911,7 +911,17 @@ __device__ __forceinline__ void dkdv_roll_unit(const BwdArgs& a, int nkb, uint32
         }
       }
     };
-    // Blocks 0 .. 4 in flight, block 0 visible.
+    // Zeros in the last slot: the block that the body before block 0's update runs over.
+    // (Weights of zero times block 0's own rows would turn an infinite dO into NaN.) Then
+    // blocks 0 .. 4 in flight, the zeros and block 0 visible.
+    const int left0 = left;
+    left = 0;
+    ld_off = (kRing - 1) * kSlot * 2;
+#pragma unroll
+    for (int i = 0; i < kLd; ++i) load_part(i);
+    load_rows();
+    left = left0;
+    ld_off = 0;
 #pragma unroll
     for (int j = 0; j < 5; ++j) {
       if (j > 0) load_advance();
@@ -967,7 +977,7 @@ __device__ __forceinline__ void dkdv_roll_unit(const BwdArgs& a, int nkb, uint32
       return tr_frag<D>(at + (q % 2 ? 0 : kBlk), ta, q / 2, c2);
     };
     bf16x8 pf[kAhead];        // the first fragments of the next phase
-    uint32_t at_c = 0, at_p = 0;  // ring offsets (elements) of block h and of block h - 1
+    uint32_t at_c = 0, at_p = (kRing - 1) * kSlot;  // ring offsets (elements) of blocks h and h - 1
     auto body = [&](auto parc) {
       constexpr int par = decltype(parc)::value;
       const uint32_t at_n = at_c == (kRing - 1) * kSlot ? 0 : at_c + kSlot;
@@ -1031,7 +1041,7 @@ __device__ __forceinline__ void dkdv_roll_unit(const BwdArgs& a, int nkb, uint32
       at_p = at_c;
       at_c = at_n;
     };
-    // Before block 0 there is nothing to update: its P and dS are zero (exp2(-inf)). Blocks
+    // Before block 0 there is nothing to update: P, dS (exp2(-inf)) and rows are zero. Blocks
     // nb and nb + 1 are zeros, so the bodies past the last block add exactly nothing.
 #pragma unroll
     for (int e = 0; e < 16; ++e) {

@@ -503,3 +503,41 @@ def test_bwd_d128_one_wave_per_simd_matches_two_passes_bitwise(T, scale):
         for x, y in zip(whole, some):
             assert bool(torch.isfinite(y.float()).all())
             assert torch.equal(x[:, h:h + 8], y)
+
+
+@pytest.mark.parametrize("T", [31, 64, 129])
+def test_bwd_d128_one_wave_per_simd_infinities_as_in_two_passes(T):
+    # An infinite upstream gradient in the first 32 queries of a frame (its dV column is
+    # infinite for the keys that see it, and no other), and keys masked by a value of minus
+    # infinity (weight exactly 0): the one-pass kernel's fill and drain add zeros, not 0 x inf.
+    B, H, F, d = 1, 64, 10, 128
+    mask = om.tile_mask(F, 1, "col")
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    q, k, v, g = (torch.randn((B, H, F * T, d), generator=gen, device="cuda").to(torch.bfloat16)
+                  for _ in range(4))
+    q[..., 0] = q[..., 0].abs() + 0.5
+    k[:, 1::2, 2 * T + 1, 0] = float("-inf")
+    g[:, ::2, 3 * T + T // 2 % 32, 5] = float("inf")
+    s = torch.cuda.current_stream()
+    out = torch.empty_like(q)
+    lse = torch.empty((B, H, F * T), dtype=torch.float32, device="cuda")
+    ta.tile_attn_fwd_heads(q, k, v, out, B, H, F, T, d, mask, d ** -0.5, lse, s)
+    whole = [torch.zeros_like(q) for _ in range(3)]
+    print(f"[case] bwd d128 infinities T={T}", flush=True)
+    ta.tile_attn_bwd(q, k, v, out, g, lse, *whole, B, H, F, T, d, mask, d ** -0.5, s)
+    dv = whole[2][0].float()
+    # frame 3 is kept by its own queries only, frame 0 by all
+    seen = torch.zeros(F * T, dtype=torch.bool, device="cuda")
+    seen[:T], seen[3 * T:4 * T] = True, True
+    assert bool((dv[::2][:, seen, 5] == float("inf")).all())
+    dv[::2][:, seen, 5] = 0
+    assert bool(torch.isfinite(dv).all())
+    assert bool((dv[1::2, 2 * T + 1] == 0).all())
+    assert bool(torch.isfinite(whole[1][:, 1::2].float()).all())
+    for h in range(0, H, 8):
+        part = [x[:, h:h + 8].contiguous() for x in (q, k, v, out, g, lse)]
+        some = [torch.zeros_like(part[0]) for _ in range(3)]
+        ta.tile_attn_bwd(*part, *some, B, 8, F, T, d, mask, d ** -0.5, s)
+        for x, y in zip(whole, some):
+            assert torch.equal(x[:, h:h + 8].isnan(), y.isnan())
+            assert torch.equal(x[:, h:h + 8].nan_to_num(0.0), y.nan_to_num(0.0))
