@@ -1191,22 +1191,21 @@ void bwd_launches(const BwdArgs& a, int nblk, hipStream_t stream) {
   const dim3 threads(kBwdThreads);
   const uint32_t passes_k = split_key_pass<D>() ? 2 : 1;
   const uint32_t units = passes_k * a.n_wg_k + a.n_wg_q;
-  uint32_t most_k = 0, most_q = 0, most_all = 0;  // positions of the busiest XCD
+  uint32_t nk[8], nq[8], all[8];  // positions of each XCD
   for (int x = 0; x < 8; ++x) {
-    const uint32_t nk = a.share_k[x + 1] - a.share_k[x], nq = a.share_q[x + 1] - a.share_q[x];
-    most_k = std::max(most_k, nk);
-    most_q = std::max(most_q, nq);
-    most_all = std::max(most_all, passes_k * nk + nq);
+    nk[x] = a.share_k[x + 1] - a.share_k[x];
+    nq[x] = a.share_q[x + 1] - a.share_q[x];
+    all[x] = passes_k * nk[x] + nq[x];
   }
   if (units <= merge_rounds<D>() * 8u * (uint32_t)a.slots_per_xcd) {
-    hipLaunchKernelGGL((bwd_all_kernel<D, PREFIX>), dim3(8 * most_all), threads, 0, stream, a, nblk);
+    hipLaunchKernelGGL((bwd_all_kernel<D, PREFIX>), dim3(grid_of(all)), threads, 0, stream, a, nblk);
     return;
   }
-  hipLaunchKernelGGL((bwd_dq_kernel<D, PREFIX>), dim3(8 * most_q), threads, 0, stream, a, nblk);
+  hipLaunchKernelGGL((bwd_dq_kernel<D, PREFIX>), dim3(grid_of(nq)), threads, 0, stream, a, nblk);
   if constexpr (split_key_pass<D>()) {
-    hipLaunchKernelGGL((bwd_dkdv_roll_kernel<D, PREFIX>), dim3(8 * most_k), threads, 0, stream, a, nblk);
+    hipLaunchKernelGGL((bwd_dkdv_roll_kernel<D, PREFIX>), dim3(grid_of(nk)), threads, 0, stream, a, nblk);
   } else {
-    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX>), dim3(8 * most_k), threads, 0, stream, a, nblk);
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, PREFIX>), dim3(grid_of(nk)), threads, 0, stream, a, nblk);
   }
 }
 

@@ -12,6 +12,18 @@ namespace ta {
 constexpr uint32_t share_count(uint32_t n, uint32_t x) { return n / 8 + (x < n % 8 ? 1u : 0u); }
 constexpr uint32_t share_start(uint32_t n, uint32_t x) { return x * (n / 8) + (x < n % 8 ? x : n % 8); }
 
+// Workgroups of a launch in which workgroup id runs position id / 8 of XCD id % 8, and XCD x
+// has count[x] positions: up to the last id that runs one. (Eight times the longest share can
+// pass the grid limit by up to seven workgroups where the units themselves just fit.)
+constexpr uint32_t grid_of(const uint32_t (&count)[8]) {
+  uint32_t grid = 0;
+  for (uint32_t x = 0; x < 8; ++x) {
+    const uint32_t end = count[x] > 0 ? 8 * (count[x] - 1) + x + 1 : 0;
+    if (end > grid) grid = end;
+  }
+  return grid;
+}
+
 // The unit that queue position pos of a share [s, e) runs when every segment of the
 // launch ends on a short query block (nqb > 1 blocks per segment, unit u = segment * nqb +
 // qb with the short block at qb = nqb - 1): the share's full blocks first, in their order,

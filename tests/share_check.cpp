@@ -133,6 +133,22 @@ static int check_cut(const char* name, int B, int H, int F, int T, int d, int g)
   return 0;
 }
 
+// The grid of a launch holds every position and no workgroup past the last: units that just
+// fit the grid limit (2^32 - 1 threads) launch whatever their number's remainder by eight.
+static int check_grid(std::vector<uint32_t> cuts) {
+  uint32_t count[8], last = 0;
+  for (uint32_t x = 0; x < 8; ++x) {
+    count[x] = cuts[x + 1] - cuts[x];
+    if (count[x] > 0) last = std::max(last, 8 * (count[x] - 1) + x);
+  }
+  const uint32_t n = cuts[8], grid = ta::grid_of(count);
+  if (grid != (n ? last + 1 : 0)) return std::printf("grid of %u units: %u\n", n, grid), 1;
+  bool equal = true;
+  for (uint32_t x = 0; x < 9; ++x) equal = equal && cuts[x] == ta::share_start(n, x);
+  if (equal && grid != n) return std::printf("grid of %u units by count: %u\n", n, grid), 1;
+  return 0;
+}
+
 int main() {
   const std::pair<int, int> col1{1, TA_MASK_COL}, sym1{1, TA_MASK_SYM}, sym2{2, TA_MASK_SYM}, col4{4, TA_MASK_COL};
   int bad = 0;
@@ -146,6 +162,13 @@ int main() {
   bad |= check("one-unit", 1, 1, 1, 7, 0, 256, {col1});
   bad |= check("few-with-rows", 1, 5, 27, 90, 663, 128, {sym2});
   bad |= check("few", 1, 3, 2, 300, 0, 256, {col1});
+  for (uint32_t n : {0u, 1u, 7u, 8u, 9u, 1000u, 16777208u, 16777209u, 16777215u}) {
+    std::vector<uint32_t> cuts(9);
+    for (uint32_t x = 0; x <= 8; ++x) cuts[x] = ta::share_start(n, x);
+    bad |= check_grid(cuts);
+  }
+  bad |= check_grid({0, 0, 5, 5, 5, 9, 30, 30, 31});
+  bad |= check_grid({0, 40, 41, 42, 43, 44, 45, 46, 46});
   bad |= check_cut("cut-d64", 1, 14, 9, 2883, 64, 5);
   bad |= check_cut("cut-d96", 1, 18, 24, 555, 96, 8);
   bad |= check_cut("cut-batch", 2, 3, 25, 2264, 64, 7);
