@@ -58,7 +58,9 @@
  *     freed and growing never waits for the stream. Later calls that fit allocate
  *     nothing and do not synchronise, so a warmed-up call can be captured in a
  *     HIP graph.
- *   - The workspace and the counters are found by the stream handle: calls on
+ *   - The workspace and the counters are found by the stream handle (and the calling
+ *     thread for hipStreamPerThread; the first such call of a thread takes over what an
+ *     ended thread left, after a wait for the device, or allocates): calls on
  *     one stream share them in stream order, calls on different live streams
  *     never share them. Two cases do share them with work that may still run,
  *     so avoid them: a stream destroyed with calls still pending whose handle a

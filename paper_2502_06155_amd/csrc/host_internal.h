@@ -100,6 +100,10 @@ int enqueue_fwd(const void* q, const void* k, const void* v, void* out, int B, i
                 int T, int d, int P, const DeviceWorkList& plan, float* ws, float scale,
                 float* lse, void* stream, int* queue, int slots_x);
 
+// hipStreamPerThread is one handle for a stream of each thread: a number of the calling thread
+// that no other thread gets, also after it has ended. 0 for any other handle.
+uint64_t stream_owner(void* stream);
+
 // The forward queue counters of (dev, stream): allocated and zeroed on first use.
 int queue_for(int dev, void* stream, int** out);
 

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cfloat>
 #include <cmath>
 #include <cstdint>
@@ -557,18 +558,22 @@ int work_list_for(const uint8_t* masks, int n_masks, int H, int F, bool allow_sp
   return TA_OK;
 }
 
+// Also where the question itself fails.
+bool is_capturing(void* stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  const bool no = hipStreamIsCapturing(static_cast<hipStream_t>(stream), &cs) == hipSuccess &&
+                  cs == hipStreamCaptureStatusNone;
+  if (!no) (void)hipGetLastError();
+  return !no;
+}
+
 // The call has enqueued every kernel that reads the plan on `stream` (or failed to). Where the
 // stream is being captured into a graph that may replay at any later time, the plan is kept
 // for the rest of the process.
 void end_plan_use(PlanUse& u, void* stream) {
   if (!u.slot) return;
   std::lock_guard<std::mutex> lock(g_cache_mutex);
-  const hipStream_t s = static_cast<hipStream_t>(stream);
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    g_cache.pin(u.slot);
-  }
+  if (is_capturing(stream)) g_cache.pin(u.slot);
   g_cache.release(u.slot);
   u.slot = nullptr;
 }
@@ -605,8 +610,61 @@ struct Workspace {
   size_t bytes = 0;
   std::vector<void*> retired;
   int* queue = nullptr;  // the forward kernel's work-queue counters, never replaced
+  bool captured = false;  // a graph may hold it: never left to another thread
 };
-std::map<std::pair<int, void*>, Workspace> g_workspaces;
+// By device, stream handle and stream_owner(). The two containers are never destroyed:
+// threads may still end while the process exits.
+using WorkspaceKey = std::pair<std::pair<int, void*>, uint64_t>;
+std::map<WorkspaceKey, Workspace>& g_workspaces = *new std::map<WorkspaceKey, Workspace>;
+// Of threads that have ended, by device: the next thread to need one takes it over.
+std::multimap<int, Workspace>& g_left_workspaces = *new std::multimap<int, Workspace>;
+
+// A number no other thread has had. At its end the thread leaves its workspaces to others.
+struct ThreadNumber {
+  uint64_t number;
+  ThreadNumber() {
+    static std::atomic<uint64_t> last{0};
+    number = ++last;
+  }
+  ~ThreadNumber() {
+    std::lock_guard<std::mutex> lock(g_cache_mutex);
+    for (auto it = g_workspaces.begin(); it != g_workspaces.end();) {
+      if (it->first.second == number && !it->second.captured) {
+        g_left_workspaces.emplace(it->first.first.first, std::move(it->second));
+        it = g_workspaces.erase(it);
+      } else {
+        ++it;
+      }
+    }
+  }
+};
+
+uint64_t stream_owner(void* stream) {
+  if (stream != (void*)hipStreamPerThread) return 0;
+  thread_local ThreadNumber mine;
+  return mine.number;
+}
+
+// The workspace of (dev, stream), with g_cache_mutex held and owner = stream_owner(stream). A
+// thread new to its stream takes over what an ended thread left, once the device is idle (the
+// ended thread's last calls may still run).
+Workspace& workspace_of(int dev, void* stream, uint64_t owner) {
+  const WorkspaceKey key{{dev, stream}, owner};
+  if (owner == 0) return g_workspaces[key];
+  const bool capturing = is_capturing(stream);
+  auto it = g_workspaces.find(key);
+  if (it == g_workspaces.end()) {
+    auto left = capturing ? g_left_workspaces.end() : g_left_workspaces.find(dev);
+    if (left != g_left_workspaces.end() && HipPlanOps::on_device(dev, [] { return hipDeviceSynchronize(); })) {
+      it = g_workspaces.emplace(key, std::move(left->second)).first;
+      g_left_workspaces.erase(left);
+    } else {
+      it = g_workspaces.emplace(key, Workspace()).first;
+    }
+  }
+  it->second.captured |= capturing;
+  return it->second;
+}
 
 // Largest workspace a call may use; masks that would need more are not split.
 constexpr size_t kMaxWorkspaceBytes = size_t(2) << 30;
@@ -642,8 +700,9 @@ int check_args(const void* q, const void* k, const void* v, void* out, int B, in
 
 
 int queue_for(int dev, void* stream, int** out) {
+  const uint64_t owner = stream_owner(stream);
   std::lock_guard<std::mutex> lock(g_cache_mutex);
-  Workspace& ws = g_workspaces[{dev, stream}];
+  Workspace& ws = workspace_of(dev, stream, owner);
   if (!ws.queue) {
     void* p = nullptr;
     hipError_t e = hipMalloc(&p, 64 * sizeof(int));
@@ -665,8 +724,9 @@ int queue_for(int dev, void* stream, int** out) {
 // enqueued by another thread that was handed it, never sees it freed, and nothing
 // has to wait for the stream.
 int workspace_for(int dev, void* stream, size_t bytes, void** out) {
+  const uint64_t owner = stream_owner(stream);
   std::lock_guard<std::mutex> lock(g_cache_mutex);
-  Workspace& ws = g_workspaces[{dev, stream}];
+  Workspace& ws = workspace_of(dev, stream, owner);
   if (ws.bytes < bytes) {
     size_t size = std::max(bytes, ws.bytes + ws.bytes / 2);
     void* p = nullptr;

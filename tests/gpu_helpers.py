@@ -12,6 +12,12 @@ MEAN_ABS = 2e-3
 REL_RMS = 1e-2
 
 
+def hip_library() -> str:
+    """The path of the HIP runtime this process has loaded."""
+    with open("/proc/self/maps") as f:
+        return next(line.split()[-1] for line in f if "libamdhip64.so" in line)
+
+
 def to_dev(bits: np.ndarray):
     import torch
 

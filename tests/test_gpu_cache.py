@@ -8,7 +8,7 @@ import pytest
 
 import workloads
 from oracle import attention as oa
-from tests.gpu_helpers import assert_parity, from_dev, to_dev, widen
+from tests.gpu_helpers import assert_parity, from_dev, hip_library, to_dev, widen
 
 pytestmark = pytest.mark.gpu
 
@@ -19,12 +19,6 @@ if not torch.cuda.is_available():
 import paper_2502_06155_amd as ta  # noqa: E402
 
 CAP = 256  # TA_PLAN_CACHE_ENTRIES
-
-
-def _hip_library() -> str:
-    """The path of the HIP runtime this process has loaded."""
-    with open("/proc/self/maps") as f:
-        return next(line.split()[-1] for line in f if "libamdhip64.so" in line)
 
 
 def test_many_masks_stay_within_the_cache_and_evicted_plans_still_work():
@@ -131,7 +125,7 @@ def test_plans_last_used_on_a_quiet_stream_are_freed():
 def test_plans_used_on_destroyed_streams_are_freed():
     # Plans last used on streams that are synchronised and destroyed, whose handles later
     # streams may receive: eviction asks nothing of a stream, so they are freed as any others.
-    hip = ctypes.CDLL(_hip_library())
+    hip = ctypes.CDLL(hip_library())
     B, H, F, T, d = 1, 1, 8, 20, 64
     qb, kb, vb = workloads.make_qkv(B, H, F, T, d, seed=170)
     q, k, v = (to_dev(x) for x in (qb, kb, vb))

@@ -3,6 +3,7 @@ first calls for each thread's masks build their kept lists concurrently, and spl
 rows use per-stream workspaces. Every result must equal, bit for bit, the same call
 made alone afterwards; those lone results are checked against the float64 oracle,
 so a kept list corrupted while it was built would not go unnoticed."""
+import ctypes
 import threading
 
 import numpy as np
@@ -11,7 +12,7 @@ import pytest
 import workloads
 from oracle import attention as oa
 from oracle import backward as ob
-from tests.gpu_helpers import assert_parity, from_dev, to_dev, widen
+from tests.gpu_helpers import assert_parity, from_dev, hip_library, to_dev, widen
 
 pytestmark = pytest.mark.gpu
 
@@ -120,3 +121,59 @@ def test_threads_on_own_streams_match_lone_calls():
         refs = ob.attention_backward(qb, kb, vb, gb, c["masks"], c["T"], c["scale"])
         for name, a, r in zip(("dq", "dk", "dv"), ref_grads, refs):
             _assert_grad(a, r, f"thread-case-{i}-{name}")
+
+
+PER_THREAD = 2  # hipStreamPerThread: one handle, a stream of its own in every thread
+
+
+def test_threads_on_the_per_thread_stream_do_not_share_a_workspace():
+    # Gradients keep the row statistics and the split rows' partials in a workspace of their
+    # stream; under one handle, each thread needs its own. Threads that come after others have
+    # ended take over theirs, so eighty short-lived ones hold no more memory than four.
+    c = _case(1)
+    dev = _device_case(c)
+    ro, rl, rg = _outputs(dev[0], 1)
+    _call(c, dev, ro[0], rl[0], rg[0], torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    want = [from_dev(x) for x in [ro[0]] + rg[0]]
+    bufs = [_outputs(dev[0], N_ITER) for _ in range(N_THREADS)]
+    torch.cuda.synchronize()
+    errors = []
+    hip = ctypes.CDLL(hip_library())
+
+    def worker(i, n, barrier=None):
+        try:
+            out, lse, grads = bufs[i]
+            if barrier is not None:
+                barrier.wait(timeout=60)
+            for it in range(n):
+                _call(c, dev, out[it], lse[it], grads[it], PER_THREAD)
+            assert hip.hipStreamSynchronize(ctypes.c_void_p(PER_THREAD)) == 0
+        except Exception as e:  # reported by the main thread
+            errors.append((i, repr(e)))
+
+    def run(n, together=True):
+        barrier = threading.Barrier(N_THREADS) if together else None
+        threads = [threading.Thread(target=worker, args=(i, n, barrier)) for i in range(N_THREADS)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join(timeout=120)
+        assert not any(t.is_alive() for t in threads), "a worker thread did not finish"
+        assert not errors, errors
+
+    print(f"[case] {N_THREADS} threads on hipStreamPerThread", flush=True)
+    run(N_ITER)
+    for out, lse, grads in bufs:
+        for it in range(N_ITER):
+            for a, w in zip([out[it]] + grads[it], want):
+                assert np.array_equal(from_dev(a), w), it
+    run(1)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for _ in range(20):
+        run(1)
+    torch.cuda.synchronize()
+    assert free - torch.cuda.mem_get_info()[0] < 16 << 20
+    for out, lse, grads in bufs:
+        assert np.array_equal(from_dev(grads[0][0]), want[1])
