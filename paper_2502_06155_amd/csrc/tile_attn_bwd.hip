@@ -681,8 +681,11 @@ __device__ __forceinline__ void dkdv_unit(const BwdArgs& a, int nkb, uint32_t wo
         auto side = [&](auto ic) {
           constexpr int i = decltype(ic)::value;
           if constexpr (kWantDk && (i == 0 || i == kHalf)) dp_start(buf, i / kHalf, dp[i / kHalf]);
-          // lse2 of queries 4 q4 .. 4 q4 + 3 (entries 4 q4 ..) of half hh, read two
-          // packets before the first packet whose share needs them.
+          // lse2 of queries 4 q4 .. 4 q4 + 3 (entries 4 q4 ..) of half hh, read one packet
+          // before the first one whose share of the steps below needs them (in that packet
+          // itself for half 0 of the d = 128 dK pass). A packet earlier measured 0 to 0.3%
+          // slower at d = 96 (93-frame gradients 15.97 -> 16.02 ms), 0.7% at d = 64 (24 heads
+          // of 24 x 1200: 1.518 -> 1.529 ms) and the same at d = 128.
           static_for<8>([&](auto qc) {
             constexpr int hh = decltype(qc)::value / 4, q4 = decltype(qc)::value % 4;
             constexpr int st = hh == 0 ? kHalf : 2 * kHalf, pk = hh == 0 ? kHalf : kAcc;
@@ -1084,9 +1087,7 @@ __global__ __launch_bounds__(kBwdThreads, 1) void bwd_dkdv_roll_kernel(const Bwd
 }
 
 // One pass per launch: each XCD (the workgroups with blockIdx % 8 == x) runs a contiguous
-// share of the pass's units. (The unit bodies are separate functions; compiled so, the
-// d = 128 dK pass fits 256 VGPRs without the two spilled registers it had as one kernel
-// body, 1.2% faster.)
+// share of the pass's units.
 template <int D, bool PREFIX>
 __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dq_kernel(const BwdArgs a, int nblk) {
   using Sh = BShape<D>;
@@ -1109,12 +1110,12 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dkdv_kernel(const BwdArgs 
 
 // All passes in one launch, for calls of few rounds of workgroups: XCD x runs its share of
 // the key side's units, then of the query side's (at d = 128 the dK pass, dq, then the dV
-// pass), longest units first. As launches of their own each pass ends on a ragged round
+// pass), in each head the longest items first. As launches of their own each pass ends on a ragged round
 // with most slots empty, and a small call takes the sum of the passes' latencies. Measured
 // (launches of their own -> one launch, same process): B = 2, H = 4, 5 x 257 tokens at
-// d = 96, col g = 1 47.7 -> 38.1 us; H = 8, 10 x 700 at d = 64 137 -> 121 us; H = 6, 8 x 3600
-// at d = 128 2.304 -> 2.196 ms; H = 6, 24 x 3600 at d = 96, sym (25 rounds) 6.53 -> 6.40 ms;
-// H = 12 col (40 rounds) 8.51 -> 8.43 ms. Over many rounds the seam is nothing and the
+// d = 96, col g = 1 47.7 -> 38.1 us; H = 8, 10 x 700 at d = 64 137 -> 121 us; H = 6,
+// 24 x 3600 at d = 96, sym (25 rounds) 6.53 -> 6.40 ms; H = 12 col (40 rounds) 8.51 ->
+// 8.43 ms (d = 128: merge_rounds). Over many rounds the seam is nothing and the
 // shared kernel costs (H = 24 col, 80 rounds: 16.58 -> 16.68 ms), so longer calls keep a
 // launch per pass (merge_rounds).
 template <int D, bool PREFIX>
