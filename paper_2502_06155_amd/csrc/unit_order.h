@@ -8,8 +8,7 @@
 namespace ta {
 
 // Units of XCD x when n units are dealt out to the 8 XCDs by count, as contiguous shares:
-// XCD x owns [share_start(n, x), share_start(n, x) + share_count(n, x)).
-constexpr uint32_t share_count(uint32_t n, uint32_t x) { return n / 8 + (x < n % 8 ? 1u : 0u); }
+// XCD x owns [share_start(n, x), share_start(n, x + 1)).
 constexpr uint32_t share_start(uint32_t n, uint32_t x) { return x * (n / 8) + (x < n % 8 ? x : n % 8); }
 
 // Workgroups of a launch in which workgroup id runs position id / 8 of XCD id % 8, and XCD x
@@ -39,10 +38,6 @@ constexpr uint32_t short_last_in_share(uint32_t s, uint32_t e, uint32_t nqb, uin
     return j / (nqb - 1) * nqb + j % (nqb - 1);
   }
   return (s / nqb + (pos - n_full)) * nqb + nqb - 1;  // short blocks from s on
-}
-// The same for XCD x's share of n units dealt out by count.
-constexpr uint32_t short_last_unit(uint32_t n, uint32_t nqb, uint32_t x, uint32_t pos) {
-  return short_last_in_share(share_start(n, x), share_start(n, x) + share_count(n, x), nqb, pos);
 }
 
 }  // namespace ta

@@ -119,28 +119,45 @@ int check(const char* name, int B, int H, int F, int T, int P, int d, int g, int
   return 0;
 }
 
-// The kernel's order of a share whose segments all end on a short block
-// (ta::short_last_unit): every position maps to a distinct unit of the share, the
-// full blocks come first and the short ones last, each in their original order.
-int check_short_last(uint32_t n_items, uint32_t nqb) {
-  const uint32_t n = n_items * nqb;
-  for (uint32_t x = 0; x < 8; ++x) {
-    const uint32_t s = ta::share_start(n, x), cnt = ta::share_count(n, x);
-    std::vector<int> seen(cnt, 0);
-    long prev_full = -1, prev_short = -1;
-    bool in_short = false;
-    for (uint32_t pos = 0; pos < cnt; ++pos) {
-      const uint32_t u = ta::short_last_unit(n, nqb, x, pos);
-      if (u < s || u >= s + cnt || seen[u - s]++) return std::printf("short-last %u %u: bad unit\n", n_items, nqb), 1;
-      const bool is_short = u % nqb == nqb - 1;
-      if (in_short && !is_short) return std::printf("short-last %u %u: full after short\n", n_items, nqb), 1;
-      in_short = is_short;
-      long& prev = is_short ? prev_short : prev_full;
-      if ((long)u <= prev) return std::printf("short-last %u %u: order\n", n_items, nqb), 1;
-      prev = (long)u;
-    }
+// The kernel's order of a share [s, e) whose segments of nqb blocks all end on a short one
+// (ta::short_last_in_share): every position maps to a distinct unit of the share, the full
+// blocks come first and the short ones last, each in their original order.
+int check_short_last(uint32_t s, uint32_t e, uint32_t nqb) {
+  std::vector<int> seen(e - s, 0);
+  long prev_full = -1, prev_short = -1;
+  bool in_short = false;
+  for (uint32_t pos = 0; pos < e - s; ++pos) {
+    const uint32_t u = ta::short_last_in_share(s, e, nqb, pos);
+    if (u < s || u >= e || seen[u - s]++) return std::printf("short-last %u-%u %u: bad unit\n", s, e, nqb), 1;
+    const bool is_short = u % nqb == nqb - 1;
+    if (in_short && !is_short) return std::printf("short-last %u-%u %u: full after short\n", s, e, nqb), 1;
+    in_short = is_short;
+    long& prev = is_short ? prev_short : prev_full;
+    if ((long)u <= prev) return std::printf("short-last %u-%u %u: order\n", s, e, nqb), 1;
+    prev = (long)u;
   }
   return 0;
+}
+
+// Shares by work of a launch with one mask per head whose segments end on a short block: cut
+// anywhere, inside segments too.
+int check_short_last_by_work(int* cuts_inside) {
+  const int B = 1, H = 6, F = 24, T = 3600, rows = 256, nqb = (T + rows - 1) / rows;
+  std::vector<uint8_t> masks((size_t)H * F * F);
+  const int g[3] = {2, 1, 4}, form[3] = {TA_MASK_SYM, TA_MASK_SYM, TA_MASK_COL};
+  for (int h = 0; h < H; ++h) tile_attn_make_mask(F, g[h % 3], form[h % 3], masks.data() + (size_t)h * F * F);
+  HostWorkList hw = build_work_list(masks.data(), H, H, F, true);
+  append_fwd_schedule(hw, B, nqb, rows, 96, T, 0, F, 64, true);
+  const uint32_t n = (uint32_t)B * hw.n_items * nqb;
+  bool equal = true;
+  int bad = 0;
+  for (uint32_t x = 0; x < 8; ++x) {
+    equal = equal && hw.share[x] == ta::share_start(n, x);
+    *cuts_inside += hw.share[x] % nqb != 0;
+    bad |= check_short_last(hw.share[x], hw.share[x + 1], nqb);
+  }
+  if (equal || hw.share[0] != 0 || hw.share[8] != n) return std::printf("short-last: not by work\n"), 1;
+  return bad;
 }
 
 }  // namespace
@@ -170,11 +187,19 @@ int main() {
   bad |= check("gpu-g", 1, 32, 6, 528, 0, 64, 1, TA_MASK_COL);
   bad |= check("gpu-h", 1, 20, 6, 528, 0, 128, 1, TA_MASK_COL);
   int orders = 0;
-  for (uint32_t nqb : {2u, 3u, 15u, 29u})
-    for (uint32_t items : {1u, 3u, 7u, 8u, 9u, 57u, 576u, 1153u}) {
-      bad |= check_short_last(items, nqb);
+  for (uint32_t nqb : {2u, 3u, 15u, 29u}) {
+    for (uint32_t items : {1u, 3u, 7u, 8u, 9u, 57u, 576u, 1153u}) {  // shares by count
+      for (uint32_t x = 0; x < 8; ++x)
+        bad |= check_short_last(ta::share_start(items * nqb, x), ta::share_start(items * nqb, x + 1), nqb);
       ++orders;
     }
+    // any share: every remainder at both ends, empty and one-unit ones
+    for (uint32_t s = 0; s <= 2 * nqb; ++s)
+      for (uint32_t e = s; e <= s + 2 * nqb + 1; ++e) bad |= check_short_last(s, e, nqb);
+  }
+  int cuts_inside = 0;
+  bad |= check_short_last_by_work(&cuts_inside);
+  std::printf("short-last by work: %d cuts inside segments\n", cuts_inside);
   std::printf("short-last orders %d\n", orders);
   return bad;
 }
