@@ -26,7 +26,8 @@ HIP_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # matrix instructions write VGPRs unless an accumulator is asked for in AGPRs: in kernels
     # of more than 256 registers the default keeps every result in AGPRs and copies each
-    # score out of them
+    # score out of them (the code of all kernels but the one-wave dK/dV pass of d = 128 is
+    # the same with and without)
     "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-I", os.path.join(REPO_DIR, "include"),
 ]

@@ -76,8 +76,8 @@ void launch_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int
 // With share_tail, each XCD whose run would end in a ragged round of whole units (of
 // slots_x resident workgroups) runs that round's units in parts over the kept tiles
 // instead, one workgroup per part, merged by log-sum-exp; otherwise every unit is one
-// workgroup. Where that may happen (share_tail, no frame split, no short-block order) the
-// shares are by count, otherwise those of launch_shares. With by_length, a plan that splits no frame and whose units with rows are
+// workgroup. Where units are cut the shares are by count, otherwise those of
+// launch_shares. With by_length, a plan that splits no frame and whose units with rows are
 // not already longest first in every XCD's share runs each share longest first (table
 // entries for every unit; query blocks past their segment's end are left out).
 void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int T, int P, int F,

@@ -292,8 +292,10 @@ DeviceWorkList place_work_list(const HostWorkList& hw, void* buf) {
   return wl;
 }
 
-void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int T, int P, int F,
-                         int slots_x, bool share_tail, bool by_length) {
+// Appends the schedule for the shares in hw.share; with may_cut, ragged last rounds are cut
+// into parts where that pays.
+static void append_schedule_of_shares(HostWorkList& hw, int B, int nqb, int rows, int d, int T, int P, int F,
+                                      int slots_x, bool may_cut, bool by_length) {
   const int32_t* items = hw.words.data();
   const int32_t* cols = hw.words.data() + hw.off_cols;
   const int64_t n_items = hw.n_items;
@@ -317,23 +319,12 @@ void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int 
     const int seg_len = (P > 0 && it[1] == F) ? P : T;
     return (int64_t)(u % nqb) * rows < seg_len;
   };
-  // Where every segment ends on a query block of at most 32 rows (video only, d = 64
-  // or 96), the kernel runs those blocks on two waves, after the full blocks of each
-  // XCD's share, and they already even out the last round: no parts then.
-  const bool short_last = P == 0 && (d == 64 || d == 96) && nqb > 1 && T - (nqb - 1) * rows <= 32;
-  // Where a ragged round may be cut into parts, the shares stay by count: they decide which
-  // units are cut and into how many parts, so a plan's rounding would change with them.
-  const bool may_cut = share_tail && hw.n_heavy == 0 && !short_last;
   std::vector<int32_t> xcd(4 * 8), pieces, cut_units;
   int n_part_slots = 0;
   int64_t wg_max = 0;
   // Longest first where it changes something: a plan with split frames runs the
   // kernel's persistent loop instead (its queue takes the natural order), and a share
   // whose units with rows already come longest first keeps the contiguous form.
-  if (may_cut)
-    for (uint32_t x = 0; x <= 8; ++x) hw.share[x] = ta::share_start((uint32_t)n, x);
-  else
-    launch_shares(hw, B, nqb, rows, T, P, F, slots_x, short_last, hw.share);
   bool table = false;
   if (by_length && hw.n_heavy == 0) {
     for (int x = 0; x < 8 && !table; ++x) {
@@ -428,6 +419,31 @@ void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int 
   hw.n_part_slots = n_part_slots;
   hw.wg_per_xcd = (int)wg_max;
   hw.unit_table = table;
+}
+
+void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int T, int P, int F,
+                         int slots_x, bool share_tail, bool by_length) {
+  // Where every segment ends on a query block of at most 32 rows (video only, d = 64
+  // or 96), the kernel runs those blocks on two waves, after the full blocks of each
+  // XCD's share, and they already even out the last round: no parts then.
+  const bool short_last = P == 0 && (d == 64 || d == 96) && nqb > 1 && T - (nqb - 1) * rows <= 32;
+  // Where a ragged round is cut into parts, the shares are by count: they decide which units
+  // are cut and into how many parts, so a plan's rounding would change with them.
+  if (share_tail && hw.n_heavy == 0 && !short_last) {
+    const size_t words = hw.words.size();
+    const uint32_t n = (uint32_t)B * (uint32_t)hw.n_items * (uint32_t)nqb;
+    for (uint32_t x = 0; x <= 8; ++x) hw.share[x] = ta::share_start(n, x);
+    append_schedule_of_shares(hw, B, nqb, rows, d, T, P, F, slots_x, true, by_length);
+    uint32_t share[9];
+    if (hw.n_cut_units > 0) return;
+    launch_shares(hw, B, nqb, rows, T, P, F, slots_x, false, share);
+    if (std::equal(share, share + 9, hw.share)) return;
+    std::copy(share, share + 9, hw.share);
+    hw.words.resize(words);
+  } else {
+    launch_shares(hw, B, nqb, rows, T, P, F, slots_x, short_last, hw.share);
+  }
+  append_schedule_of_shares(hw, B, nqb, rows, d, T, P, F, slots_x, false, by_length);
 }
 
 // A cached plan and its device.

@@ -3,7 +3,7 @@
 // units in order; a launch of few units with rows, or whose counts are even to within 3% of the work,
 // keeps the equal counts; any other gets shares within one unit of an eighth of the work. Prints "<name>
 // equal 0|1 most M" with M the largest share's work over an eighth of all. It also checks that
-// append_fwd_schedule keeps the equal counts where it may cut units into parts.
+// append_fwd_schedule keeps the equal counts where it cuts units into parts.
 #include <algorithm>
 #include <cstdio>
 #include <vector>
@@ -113,23 +113,29 @@ static int check_choice(const char* name, int B, int H, int F, int T, int P, int
   return 0;
 }
 
-// A forward launch whose ragged round may be cut into parts keeps the shares by count: they
-// decide which units are cut, and with them how its sums are rounded. Prints "<name> cut U
-// units", U the units cut.
-static int check_cut(const char* name, int B, int H, int F, int T, int d, int g) {
+// A forward launch whose ragged round is cut into parts keeps the shares by count: they decide
+// which units are cut, and with them how its sums are rounded. Only one that cuts nothing by
+// count may take the shares by work, and then cuts nothing either. Prints "<name> cut U units
+// by work 0|1", U the units cut.
+static int check_cut(const char* name, int B, int H, int F, int T, int d, std::vector<std::pair<int, int>> kinds) {
   const int rows = d == 128 ? 128 : 256, nqb = (T + rows - 1) / rows;
-  std::vector<uint8_t> m((size_t)F * F);
-  tile_attn_make_mask(F, g, TA_MASK_SYM, m.data());
-  HostWorkList hw = build_work_list(m.data(), 1, H, F, true);
+  std::vector<uint8_t> masks((size_t)H * F * F);
+  for (int h = 0; h < H; ++h)
+    tile_attn_make_mask(F, kinds[h % kinds.size()].first, kinds[h % kinds.size()].second, masks.data() + (size_t)h * F * F);
+  HostWorkList hw = build_work_list(masks.data(), H, H, F, true);
+  const size_t words = hw.words.size();
   append_fwd_schedule(hw, B, nqb, rows, d, T, 0, F, 64, true);
   const uint32_t n = (uint32_t)B * hw.n_items * nqb;
   const int32_t* xcd = hw.words.data() + hw.off_xcd;
   if (hw.n_heavy != 0) return std::printf("%s: frames split\n", name), 1;
-  for (int x = 0; x < 8; ++x)
-    if (hw.share[x] != ta::share_start(n, x) || xcd[4 * x] != (int)hw.share[x])
-      return std::printf("%s: shares not by count\n", name), 1;
-  if (hw.share[8] != n) return std::printf("%s: end\n", name), 1;
-  std::printf("%s cut %d units\n", name, hw.n_cut_units);
+  bool equal = true;
+  for (int x = 0; x < 8; ++x) {
+    equal = equal && hw.share[x] == ta::share_start(n, x);
+    if (xcd[4 * x] != (int)hw.share[x]) return std::printf("%s: shares of another schedule\n", name), 1;
+  }
+  if (hw.off_xcd != words || hw.share[8] != n) return std::printf("%s: layout\n", name), 1;
+  if (!equal && (hw.n_cut_units > 0 || hw.n_part_slots > 0)) return std::printf("%s: cut by work\n", name), 1;
+  std::printf("%s cut %d units by work %d\n", name, hw.n_cut_units, (int)!equal);
   return 0;
 }
 
@@ -169,10 +175,11 @@ int main() {
   }
   bad |= check_grid({0, 0, 5, 5, 5, 9, 30, 30, 31});
   bad |= check_grid({0, 40, 41, 42, 43, 44, 45, 46, 46});
-  bad |= check_cut("cut-d64", 1, 14, 9, 2883, 64, 5);
-  bad |= check_cut("cut-d96", 1, 18, 24, 555, 96, 8);
-  bad |= check_cut("cut-batch", 2, 3, 25, 2264, 64, 7);
-  bad |= check_cut("cut-d128", 1, 13, 4, 3231, 128, 3);
+  bad |= check_cut("cut-d64", 1, 14, 9, 2883, 64, {{5, TA_MASK_SYM}});
+  bad |= check_cut("cut-d96", 1, 18, 24, 555, 96, {{8, TA_MASK_SYM}});
+  bad |= check_cut("cut-batch", 2, 3, 25, 2264, 64, {{7, TA_MASK_SYM}});
+  bad |= check_cut("cut-d128", 1, 13, 4, 3231, 128, {{3, TA_MASK_SYM}});
+  bad |= check_cut("cut-none", 3, 5, 17, 1936, 128, {{7, TA_MASK_COL}, col1, {14, TA_MASK_SYM}});
   bad |= check_choice("choice-sym4", 1, 18, 24, 555, 0, 256, false, {{4, TA_MASK_SYM}});
   bad |= check_choice("choice-fwd", 2, 18, 8, 1056, 0, 256, true, {col1, {1, TA_MASK_COL}, sym2});
   bad |= check_choice("choice-d128", 1, 36, 15, 482, 0, 128, false, {{6, TA_MASK_COL}, col1, {12, TA_MASK_SYM}});

@@ -33,8 +33,12 @@ def test_shares_hold_equal_work(tmp_path):
     assert got["uniform"][0] == 1
     for name in ("mixed-fwd", "mixed-bwd", "share-sym"):
         assert got[name][0] == 0 and got[name][1] < 1.02, name
-    cut = re.findall(r"^(cut-\S+) cut (\d+) units$", res.stdout, re.M)
-    assert len(cut) == 4 and sum(int(n) for _, n in cut) > 0
+    cut = {n: (int(u), int(w)) for n, u, w in
+           re.findall(r"^(cut-\S+) cut (\d+) units by work (\d)$", res.stdout, re.M)}
+    assert len(cut) == 5
+    for name in ("cut-d96", "cut-batch", "cut-d128"):
+        assert cut[name][0] > 0 and cut[name][1] == 0, name
+    assert cut["cut-none"] == (0, 1)
     # the cut by work is taken only where it makes the launch shorter
     choice = {m.group(1): tuple(float(m.group(i)) for i in (2, 3, 4))
               for m in re.finditer(r"^(choice-\S+) counts (\S+) work (\S+) chosen (\S+)$", res.stdout, re.M)}
