@@ -66,9 +66,11 @@ bool unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P
 // The shares of a forward that cuts no parts: those of unit_shares where they make the launch
 // shorter (to within half a percent), each XCD running its share in order on `slots`
 // workgroups at a time (with short_last its full blocks first), else by count.
+// With every_call (nothing is kept for the next call) the rule is cheap where units are short.
 constexpr int64_t kMaxModelledUnits = 32 * 8 * 64;
+constexpr int64_t kMinTilesEveryCall = 128;
 void launch_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, int slots,
-                   bool short_last, uint32_t share[9]);
+                   bool short_last, bool every_call, uint32_t share[9]);
 
 // Appends the forward launch schedule to hw (see FwdArgs::sched): B batch entries, nqb
 // query blocks of `rows` rows per segment, head dimension d, T tokens per frame and P
@@ -79,9 +81,10 @@ void launch_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int
 // workgroup. Where units are cut the shares are by count, otherwise those of
 // launch_shares. With by_length, a plan that splits no frame and whose units with rows are
 // not already longest first in every XCD's share runs each share longest first (table
-// entries for every unit; query blocks past their segment's end are left out).
+// entries for every unit; query blocks past their segment's end are left out). every_call:
+// see launch_shares.
 void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int T, int P, int F,
-                         int slots_x, bool share_tail, bool by_length = false);
+                         int slots_x, bool share_tail, bool by_length = false, bool every_call = false);
 
 // Plans H heads with n_masks masks (1: shared, H: one per head) of F segments; heavy
 // query frames are split into pieces when allow_split.

@@ -184,6 +184,7 @@ bool unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P
   const UnitWork uw(hw, B, nblk, rows, T, P, F);
   const int64_t n_items = uw.n_items, per_b = uw.per_b, n = uw.n;
   for (uint32_t x = 0; x <= 8; ++x) share[x] = ta::share_start((uint32_t)n, x);
+  if (n < kMinUnitsByWork) return false;
   std::vector<int64_t> before((size_t)n_items + 1, 0);  // work of the items before i
   int64_t with_rows = 0;
   for (int64_t i = 0; i < n_items; ++i) {
@@ -254,10 +255,13 @@ int64_t modelled_time(const UnitWork& uw, const uint32_t share[9], int slots, bo
 // process): where the model says no 0.93 to 1.12, 1.016 on average (H = 29, 9 x 775 at d = 96
 // 401.5 -> 439.6 us); else 0.69 to 1.04, 0.95 on average. The model costs about 25 ns of host
 // time per unit and cut, so launches of more than 32 rounds, where at most a few percent are
-// open, stay by count instead. The gradients, whose passes share a launch or come as two long
+// open, stay by count instead, and so do launches of short units where this is done anew on
+// every call (fewer than 128 tiles of at least 1.9 us a unit: the model would take over a tenth
+// of the launch; 2 x 30 heads of 40 x 100 at d = 96, one mask per head, host time of a call's
+// schedule 7 us without the model, 90 us with it). The gradients, whose passes share a launch or come as two long
 // ones, are shorter by work whatever the model says (51 shapes: 0.67 to 1.03, 0.95 on average).
 void launch_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, int slots,
-                   bool short_last, uint32_t share[9]) {
+                   bool short_last, bool every_call, uint32_t share[9]) {
   int64_t most_count = 0, most_work = 0, longest = 0;
   if (!unit_shares(hw, B, nblk, rows, T, P, F, share, &most_count, &most_work)) return;
   const UnitWork uw(hw, B, nblk, rows, T, P, F);
@@ -265,7 +269,7 @@ void launch_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int
   if (most_work + slots * longest <= most_count) return;
   uint32_t count[9];
   for (uint32_t x = 0; x <= 8; ++x) count[x] = ta::share_start((uint32_t)uw.n, x);
-  if (uw.n > kMaxModelledUnits ||
+  if (uw.n > kMaxModelledUnits || (every_call && 8 * most_work < 2 * kMinTilesEveryCall * uw.n) ||
       200 * modelled_time(uw, share, slots, short_last) > 201 * modelled_time(uw, count, slots, short_last))
     std::copy(count, count + 9, share);
 }
@@ -422,7 +426,7 @@ static void append_schedule_of_shares(HostWorkList& hw, int B, int nqb, int rows
 }
 
 void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int T, int P, int F,
-                         int slots_x, bool share_tail, bool by_length) {
+                         int slots_x, bool share_tail, bool by_length, bool every_call) {
   // Where every segment ends on a query block of at most 32 rows (video only, d = 64
   // or 96), the kernel runs those blocks on two waves, after the full blocks of each
   // XCD's share, and they already even out the last round: no parts then.
@@ -436,12 +440,12 @@ void append_fwd_schedule(HostWorkList& hw, int B, int nqb, int rows, int d, int 
     append_schedule_of_shares(hw, B, nqb, rows, d, T, P, F, slots_x, true, by_length);
     uint32_t share[9];
     if (hw.n_cut_units > 0) return;
-    launch_shares(hw, B, nqb, rows, T, P, F, slots_x, false, share);
+    launch_shares(hw, B, nqb, rows, T, P, F, slots_x, false, every_call, share);
     if (std::equal(share, share + 9, hw.share)) return;
     std::copy(share, share + 9, hw.share);
     hw.words.resize(words);
   } else {
-    launch_shares(hw, B, nqb, rows, T, P, F, slots_x, short_last, hw.share);
+    launch_shares(hw, B, nqb, rows, T, P, F, slots_x, short_last, every_call, hw.share);
   }
   append_schedule_of_shares(hw, B, nqb, rows, d, T, P, F, slots_x, false, by_length);
 }

@@ -91,7 +91,7 @@ extern "C" int tile_attn_fwd_heads_noalloc(const void* q, const void* k, const v
   HostWorkList hw = build_work_list(tile_masks, n_masks, H, F, true);
   if ((size_t)hw.n_slots * B * T * (d + 1) > kPartialFloats || (int64_t)B * hw.n_items * nqb > max_wg)
     hw = build_work_list(tile_masks, n_masks, H, F, false);
-  append_fwd_schedule(hw, B, (int)nqb, rows, d, T, 0, F, slots_x, false);
+  append_fwd_schedule(hw, B, (int)nqb, rows, d, T, 0, F, slots_x, false, false, /*every_call=*/true);
   if (hw.words.size() > kPlanWords)
     return fail(TA_ERR_BAD_SHAPE, "the work plan needs " + std::to_string(hw.words.size()) +
                                       " words, more than the " + std::to_string(kPlanWords) +

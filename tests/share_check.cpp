@@ -104,7 +104,7 @@ static int check_choice(const char* name, int B, int H, int F, int T, int P, int
   uint32_t count[9], work[9], chosen[9];
   for (uint32_t x = 0; x <= 8; ++x) count[x] = ta::share_start(n, x);
   unit_shares(hw, B, nblk, rows, T, P, F, work);
-  launch_shares(hw, B, nblk, rows, T, P, F, 64, short_last, chosen);
+  launch_shares(hw, B, nblk, rows, T, P, F, 64, short_last, false, chosen);
   if (!std::equal(chosen, chosen + 9, count) && !std::equal(chosen, chosen + 9, work))
     return std::printf("%s: neither cut\n", name), 1;
   const double c = longest(count), w = longest(work), m = longest(chosen);
@@ -136,6 +136,24 @@ static int check_cut(const char* name, int B, int H, int F, int T, int d, std::v
   if (hw.off_xcd != words || hw.share[8] != n) return std::printf("%s: layout\n", name), 1;
   if (!equal && (hw.n_cut_units > 0 || hw.n_part_slots > 0)) return std::printf("%s: cut by work\n", name), 1;
   std::printf("%s cut %d units by work %d\n", name, hw.n_cut_units, (int)!equal);
+  return 0;
+}
+
+// A schedule formed on every call takes the cut by work only where a bound says so, or, with long
+// units, the model. Prints "<name> every call work 0|1".
+static int check_every_call(const char* name, int B, int H, int F, int T, int d, std::vector<std::pair<int, int>> kinds) {
+  const int rows = d == 128 ? 128 : 256, nqb = (T + rows - 1) / rows;
+  std::vector<uint8_t> masks((size_t)H * F * F);
+  for (int h = 0; h < H; ++h)
+    tile_attn_make_mask(F, kinds[h % kinds.size()].first, kinds[h % kinds.size()].second, masks.data() + (size_t)h * F * F);
+  HostWorkList kept = build_work_list(masks.data(), H, H, F, true), hw = kept;
+  append_fwd_schedule(kept, B, nqb, rows, d, T, 0, F, 64, false, false);
+  append_fwd_schedule(hw, B, nqb, rows, d, T, 0, F, 64, false, false, true);
+  const uint32_t n = (uint32_t)B * hw.n_items * nqb;
+  bool equal = true;
+  for (uint32_t x = 0; x <= 8; ++x) equal = equal && hw.share[x] == ta::share_start(n, x);
+  if (!equal && !std::equal(hw.share, hw.share + 9, kept.share)) return std::printf("%s: another cut\n", name), 1;
+  std::printf("%s every call work %d\n", name, (int)!equal);
   return 0;
 }
 
@@ -180,6 +198,9 @@ int main() {
   bad |= check_cut("cut-batch", 2, 3, 25, 2264, 64, {{7, TA_MASK_SYM}});
   bad |= check_cut("cut-d128", 1, 13, 4, 3231, 128, {{3, TA_MASK_SYM}});
   bad |= check_cut("cut-none", 3, 5, 17, 1936, 128, {{7, TA_MASK_COL}, col1, {14, TA_MASK_SYM}});
+  bad |= check_every_call("every-share", 1, 6, 24, 3600, 96, {sym2, sym1, col4});
+  bad |= check_every_call("every-long", 3, 5, 17, 1936, 128, {{7, TA_MASK_COL}, col1, {14, TA_MASK_SYM}});
+  bad |= check_every_call("every-short", 2, 30, 40, 100, 96, {{3, TA_MASK_COL}, col1, {6, TA_MASK_SYM}});
   bad |= check_choice("choice-sym4", 1, 18, 24, 555, 0, 256, false, {{4, TA_MASK_SYM}});
   bad |= check_choice("choice-fwd", 2, 18, 8, 1056, 0, 256, true, {col1, {1, TA_MASK_COL}, sym2});
   bad |= check_choice("choice-d128", 1, 36, 15, 482, 0, 128, false, {{6, TA_MASK_COL}, col1, {12, TA_MASK_SYM}});

@@ -39,6 +39,8 @@ def test_shares_hold_equal_work(tmp_path):
     for name in ("cut-d96", "cut-batch", "cut-d128"):
         assert cut[name][0] > 0 and cut[name][1] == 0, name
     assert cut["cut-none"] == (0, 1)
+    every = dict(re.findall(r"^(every-\S+) every call work (\d)$", res.stdout, re.M))
+    assert every == {"every-share": "1", "every-long": "1", "every-short": "0"}
     # the cut by work is taken only where it makes the launch shorter
     choice = {m.group(1): tuple(float(m.group(i)) for i in (2, 3, 4))
               for m in re.finditer(r"^(choice-\S+) counts (\S+) work (\S+) chosen (\S+)$", res.stdout, re.M)}
