@@ -229,20 +229,23 @@ bool unit_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P
 // `slots` workgroups at a time (with short_last the full blocks first).
 int64_t modelled_time(const UnitWork& uw, const uint32_t share[9], int slots, bool short_last) {
   int64_t longest = 0;
-  std::vector<int64_t> busy;
+  std::vector<int64_t> line;  // from `head` on, the times at which the slots are free, soonest first
   for (int x = 0; x < 8; ++x) {
     const uint32_t s = share[x], e = share[x + 1];
-    busy.assign(slots, 0);  // a heap of the times at which the slots are free, soonest first
-    for (uint32_t pos = 0; pos < e - s; ++pos) {
+    line.assign(slots, 0);
+    line.reserve(slots + (e - s));
+    for (uint32_t pos = 0, head = 0; pos < e - s; ++pos) {
       const uint32_t u = short_last ? ta::short_last_in_share(s, e, (uint32_t)uw.nblk, pos) : s + pos;
       const uint32_t rem = u % (uint32_t)uw.per_b;
       const int64_t work = uw.unit(rem / (uint32_t)uw.nblk, rem % (uint32_t)uw.nblk);
       if (work == 0) continue;
-      std::pop_heap(busy.begin(), busy.end(), std::greater<int64_t>());
-      busy.back() += work;
-      longest = std::max(longest, busy.back());
-      std::push_heap(busy.begin(), busy.end(), std::greater<int64_t>());
+      const int64_t end = line[head++] + work;  // mostly the last of all, or near it
+      size_t at = line.size();
+      line.push_back(end);
+      for (; at > head && line[at - 1] > end; --at) line[at] = line[at - 1];
+      line[at] = end;
     }
+    longest = std::max(longest, line.back());
   }
   return longest;
 }
@@ -253,13 +256,14 @@ int64_t modelled_time(const UnitWork& uw, const uint32_t share[9], int slots, bo
 // would be even if its longest unit came last (in-order dispatch to the first free slot ends
 // by then), else by the model. Measured (59 shapes of 2 to 13 rounds, by work over by count, one
 // process): where the model says no 0.93 to 1.12, 1.016 on average (H = 29, 9 x 775 at d = 96
-// 401.5 -> 439.6 us); else 0.69 to 1.04, 0.95 on average. The model costs about 25 ns of host
+// 401.5 -> 439.6 us); else 0.69 to 1.04, 0.95 on average. The model costs 9 to 20 ns of host
 // time per unit and cut, so launches of more than 32 rounds, where at most a few percent are
 // open, stay by count instead, and so do launches of short units where this is done anew on
-// every call (fewer than 128 tiles of at least 1.9 us a unit: the model would take over a tenth
-// of the launch; 2 x 30 heads of 40 x 100 at d = 96, one mask per head, host time of a call's
-// schedule 7 us without the model, 90 us with it). The gradients, whose passes share a launch or come as two long
-// ones, are shorter by work whatever the model says (51 shapes: 0.67 to 1.03, 0.95 on average).
+// every call: under 128 tiles of at least 1.9 us a unit the model could take more than a
+// twentieth of the launch (2 x 30 heads of 40 x 100 at d = 96, one mask per head: 7 us of host
+// time for a call's schedule without it, 61 us with it, for a launch of 230 us). The
+// gradients, whose passes share a launch or come as two long ones, are shorter by work whatever
+// the model says (51 shapes: 0.67 to 1.03, 0.95 on average).
 void launch_shares(const HostWorkList& hw, int B, int nblk, int rows, int T, int P, int F, int slots,
                    bool short_last, bool every_call, uint32_t share[9]) {
   int64_t most_count = 0, most_work = 0, longest = 0;
