@@ -37,6 +37,7 @@ struct DeviceWorkList {
   int n_cut_units = 0, n_part_slots = 0, wg_per_xcd = 0;
   bool unit_table = false;  // every position is a table entry (no contiguous whole units)
   uint32_t share[9] = {};   // the XCDs' contiguous shares of the units
+  int64_t kept = 0;         // kept entries of all items
 };
 
 // The same plan as host words, before upload: offsets of the parts in words.
@@ -48,6 +49,7 @@ struct HostWorkList {
   int n_cut_units = 0, n_part_slots = 0, wg_per_xcd = 0;
   bool unit_table = false;
   uint32_t share[9] = {};
+  int64_t kept = 0;
 };
 
 // Workgroups a forward launch keeps resident per XCD (two per compute unit).

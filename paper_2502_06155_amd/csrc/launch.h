@@ -116,6 +116,7 @@ struct BwdArgs {
   // The XCDs' contiguous shares of each side's units: XCD x runs [share[x], share[x + 1]).
   uint32_t share_q[9], share_k[9];
   int slots_per_xcd;  // workgroups of the gradient kernels resident per XCD
+  int key_blocks;     // 32-query blocks per item of the key side, on average
 };
 
 // Adds the partials of split segments, of up to three gradients in one launch: heavy holds

@@ -23,7 +23,8 @@
 //         the frames that keep it (the work list of the transposed mask):
 //         S = Q K^T, dP = dO V^T, dV^T += dO^T P, dK^T += Q^T dS. Each lane owns
 //         one key of its wave's 32-key column block.
-//         At d = 128 large calls run it with one wave per SIMD (dkdv_roll_unit).
+//         At d = 128 large calls of long units run it with one wave per SIMD
+//         (dkdv_roll_unit).
 //   sum   adds the fp32 partials of frames the work plan split into pieces.
 // Small calls run dq and dk/dv in one launch (bwd_all_kernel).
 // dq is recomputed in its own pass instead of being accumulated from the key side:
@@ -65,14 +66,15 @@ constexpr int kBwdThreads = 64 * kBwdWaves;
 // rows per wave at one workgroup per CU (which halves the LDS fragment reads per
 // MFMA but puts the accumulators in AGPRs, copies the scores out of them and
 // serialises the vector work) by 17% (dq) and 12% (dk/dv). Both passes at d = 128 as well
-// own 32 rows per wave; large calls run the dk/dv pass with one wave per SIMD there.
+// own 32 rows per wave; large calls of long units run the dk/dv pass with one wave per
+// SIMD there.
 constexpr int kRowsPerWg = kBwdWaves * 32;
 
 // What one pass of the key side produces. At d = 128 dK and dV together do not fit 256
 // VGPRs (their accumulators, K and V operands alone take 192): in the shared launch of
 // small calls, whose kernel runs at two workgroups per CU, the key side is two passes
-// there (dV: S and P only; dK: S, dP and dS) that form S twice; larger calls run
-// dkdv_roll_unit.
+// there (dV: S and P only; dK: S, dP and dS) that form S twice; larger calls
+// of long units (kMinRollBlocks) run dkdv_roll_unit.
 enum KeyPass { kDkDv = 0, kDvOnly = 1, kDkOnly = 2 };
 template <int D>
 constexpr bool split_key_pass() { return D == 128; }
@@ -84,6 +86,15 @@ constexpr bool split_key_pass() { return D == 128; }
 // 235 and 233; H = 16: 447 and 430; H = 24, 12 x 900, sym: 2.11 and 1.87 ms).
 template <int D>
 constexpr uint32_t merge_rounds() { return D == 128 ? 3 : 48; }
+
+// Calls at d = 128 whose key-side units walk fewer 32-query blocks than this on average stay in
+// the shared launch however many rounds they are: dkdv_roll_unit, alone on its compute unit,
+// hides nothing of a unit's start (five blocks loaded ahead) and end. Measured (shared launch
+// and dkdv_roll_unit, same process): 2 x 37 heads of 47 x 37, col, 3, 9 and 17 blocks: 210
+// and 257 us, 317 and 380, 447 and 513; 2 x 20 heads of 40 x 128, 15 and 31: 343 and 378, 497
+// and 498; 40 x 100, 35: 476 and 477; 24 heads of 24 x 512, 31 and 46: 677 and 678, 929 and 877;
+// 12 heads of 40 x 200, 34: 300 and 286.
+constexpr int kMinRollBlocks = 32;
 
 template <int D>
 struct BShape {
@@ -1117,7 +1128,7 @@ __global__ __launch_bounds__(kBwdThreads, 2) void bwd_dkdv_kernel(const BwdArgs 
 // 24 x 3600 at d = 96, sym (25 rounds) 6.53 -> 6.40 ms; H = 12 col (40 rounds) 8.51 ->
 // 8.43 ms (d = 128: merge_rounds). Over many rounds the seam is nothing and the
 // shared kernel costs (H = 24 col, 80 rounds: 16.58 -> 16.68 ms), so longer calls keep a
-// launch per pass (merge_rounds).
+// launch per pass (merge_rounds; kMinRollBlocks).
 template <int D, bool PREFIX>
 __global__ __launch_bounds__(kBwdThreads, 2) void bwd_all_kernel(const BwdArgs a, int nblk) {
   using Sh = BShape<D>;
@@ -1198,7 +1209,9 @@ void bwd_launches(const BwdArgs& a, int nblk, hipStream_t stream) {
     nq[x] = a.share_q[x + 1] - a.share_q[x];
     all[x] = passes_k * nk[x] + nq[x];
   }
-  if (units <= merge_rounds<D>() * 8u * (uint32_t)a.slots_per_xcd) {
+  const bool few = units <= merge_rounds<D>() * 8u * (uint32_t)a.slots_per_xcd;
+  const bool fits = (uint64_t)grid_of(all) * kBwdThreads <= UINT32_MAX;
+  if (few || (split_key_pass<D>() && a.key_blocks < kMinRollBlocks && fits)) {
     hipLaunchKernelGGL((bwd_all_kernel<D, PREFIX>), dim3(grid_of(all)), threads, 0, stream, a, nblk);
     return;
   }

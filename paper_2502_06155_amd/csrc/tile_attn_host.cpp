@@ -138,6 +138,7 @@ HostWorkList build_work_list(const uint8_t* masks, int n_masks, int H, int F, bo
   hw.words.insert(hw.words.end(), heavy.begin(), heavy.end());
   if (heavy.empty()) hw.words.push_back(0);
   hw.n_items = (int)(items.size() / 5);
+  for (size_t i = 0; i < items.size(); i += 5) hw.kept += items[i + 3];
   hw.n_heavy = (int)(heavy.size() / 4);
   hw.n_slots = n_slots;
   return hw;
@@ -289,6 +290,7 @@ DeviceWorkList place_work_list(const HostWorkList& hw, void* buf) {
   wl.n_heavy = hw.n_heavy;
   wl.n_slots = hw.n_slots;
   std::copy(hw.share, hw.share + 9, wl.share);
+  wl.kept = hw.kept;
   if (hw.wg_per_xcd > 0) {
     wl.sched_xcd = w + hw.off_xcd;
     wl.cut_units = w + hw.off_cut_units;
@@ -1024,6 +1026,9 @@ int run_bwd(const void* q, const void* k, const void* v, const void* out, const 
   std::copy(wq->share, wq->share + 9, a.share_q);
   std::copy(wk->share, wk->share + 9, a.share_k);
   a.slots_per_xcd = resident_slots_per_xcd(dev);
+  int64_t blocks = wk->kept * ((T + 31) / 32);
+  if (P > 0) blocks += (int64_t)H * n_seg * ((P + 31) / 32 - (T + 31) / 32);  // every row keeps the text once
+  a.key_blocks = (int)(blocks / wk->n_items);
   e = ta::launch_bwd(a, s);
   if (e != hipSuccess) return fail(TA_ERR_HIP, std::string("gradient launch: ") + hipGetErrorString(e));
   ta::SumArgs m;

@@ -474,16 +474,19 @@ def test_bwd_launch_per_pass_matches_one_launch_bitwise(d, P):
 
 
 @pytest.mark.parametrize("scale", [128 ** -0.5, -0.1, 0.0])
+@pytest.mark.parametrize("H, F", [(64, 10), (16, 48)])
 @pytest.mark.parametrize("T", [1, 31, 32, 33, 64, 65, 129])
-def test_bwd_d128_one_wave_per_simd_matches_two_passes_bitwise(T, scale):
-    # 64 heads are 3.75 rounds of workgroups and more (dK and dV in one pass, one wave per
-    # SIMD), eight of them at most one (two passes in the shared launch). Both add the same
+def test_bwd_d128_one_wave_per_simd_matches_two_passes_bitwise(T, H, F, scale):
+    # 16 heads of 48 frames are 4.5 rounds of workgroups and more, whose keys are kept by 32
+    # blocks of queries or more on average (dK and dV in one pass, one wave per SIMD), four of
+    # them at most 2.5 (two passes in the shared launch). Both add the same
     # products in the same order, 16 queries at a time. Blocks of 32 queries and their
     # remainders, key frames that nobody keeps, query frames that keep nothing, and a heavy
-    # row and column, which are split into partials.
-    B, H, F, d = 1, 64, 10, 128
+    # row and column, which are split into partials from T = 33 on. 64 heads of 10 frames have
+    # as many rounds but few blocks per key: the shared launch.
+    B, d = 1, 128
     rng = np.random.default_rng(T)
-    masks = (rng.random((H, F, F)) < 0.15).astype(np.uint8)
+    masks = (rng.random((H, F, F)) < (0.15 if F == 10 else 0.4 if T > 32 else 0.8)).astype(np.uint8)
     masks[:, 4, :], masks[:, :, 7] = 1, 1
     masks[::3, 2, :], masks[::3, :, 5] = 0, 0
     gen = torch.Generator(device="cuda").manual_seed(T)
@@ -495,23 +498,31 @@ def test_bwd_d128_one_wave_per_simd_matches_two_passes_bitwise(T, scale):
     ta.tile_attn_fwd_heads(q, k, v, out, B, H, F, T, d, masks, scale, lse, s)
     whole = [torch.full_like(q, float("nan")) for _ in range(3)]
     ta.tile_attn_bwd(q, k, v, out, g, lse, *whole, B, H, F, T, d, masks, scale, s)
-    print(f"[case] bwd d128 T={T} scale={scale}", flush=True)
-    for h in range(0, H, 8):
-        part = [x[:, h:h + 8].contiguous() for x in (q, k, v, out, g, lse)]
+    print(f"[case] bwd d128 T={T} H={H} scale={scale}", flush=True)
+    n = 8 if F == 10 else 4
+    for h in range(0, H, n):
+        part = [x[:, h:h + n].contiguous() for x in (q, k, v, out, g, lse)]
         some = [torch.full_like(part[0], float("nan")) for _ in range(3)]
-        ta.tile_attn_bwd(*part, *some, B, 8, F, T, d, masks[h:h + 8], scale, s)
+        ta.tile_attn_bwd(*part, *some, B, n, F, T, d, masks[h:h + n], scale, s)
         for x, y in zip(whole, some):
             assert bool(torch.isfinite(y.float()).all())
-            assert torch.equal(x[:, h:h + 8], y)
+            assert torch.equal(x[:, h:h + n], y)
 
 
+@pytest.mark.parametrize("H, F", [(64, 10), (16, 48)])
 @pytest.mark.parametrize("T", [31, 64, 129])
-def test_bwd_d128_one_wave_per_simd_infinities_as_in_two_passes(T):
+def test_bwd_d128_one_wave_per_simd_infinities_as_in_two_passes(T, H, F):
     # An infinite upstream gradient in the first 32 queries of a frame (its dV column is
     # infinite for the keys that see it, and no other), and keys masked by a value of minus
     # infinity (weight exactly 0): the one-pass kernel's fill and drain add zeros, not 0 x inf.
-    B, H, F, d = 1, 64, 10, 128
+    # 48 frames of 39 or 40 kept ones run it, ten of one or two the shared launch.
+    B, d = 1, 128
     mask = om.tile_mask(F, 1, "col")
+    if F == 48:
+        i, j = np.indices((F, F))
+        mask[(j - i) % F < 39] = 1
+        mask[:, 47] = mask[:, 46] = 0
+        mask[:, 0] = 1
     gen = torch.Generator(device="cuda").manual_seed(T)
     q, k, v, g = (torch.randn((B, H, F * T, d), generator=gen, device="cuda").to(torch.bfloat16)
                   for _ in range(4))
@@ -523,21 +534,20 @@ def test_bwd_d128_one_wave_per_simd_infinities_as_in_two_passes(T):
     lse = torch.empty((B, H, F * T), dtype=torch.float32, device="cuda")
     ta.tile_attn_fwd_heads(q, k, v, out, B, H, F, T, d, mask, d ** -0.5, lse, s)
     whole = [torch.zeros_like(q) for _ in range(3)]
-    print(f"[case] bwd d128 infinities T={T}", flush=True)
+    print(f"[case] bwd d128 infinities T={T} H={H}", flush=True)
     ta.tile_attn_bwd(q, k, v, out, g, lse, *whole, B, H, F, T, d, mask, d ** -0.5, s)
     dv = whole[2][0].float()
-    # frame 3 is kept by its own queries only, frame 0 by all
-    seen = torch.zeros(F * T, dtype=torch.bool, device="cuda")
-    seen[:T], seen[3 * T:4 * T] = True, True
+    seen = torch.from_numpy(np.repeat(mask[3] != 0, T)).cuda()  # the keys that frame 3's queries keep
     assert bool((dv[::2][:, seen, 5] == float("inf")).all())
     dv[::2][:, seen, 5] = 0
     assert bool(torch.isfinite(dv).all())
     assert bool((dv[1::2, 2 * T + 1] == 0).all())
     assert bool(torch.isfinite(whole[1][:, 1::2].float()).all())
-    for h in range(0, H, 8):
-        part = [x[:, h:h + 8].contiguous() for x in (q, k, v, out, g, lse)]
+    n = 8 if F == 10 else 4
+    for h in range(0, H, n):
+        part = [x[:, h:h + n].contiguous() for x in (q, k, v, out, g, lse)]
         some = [torch.zeros_like(part[0]) for _ in range(3)]
-        ta.tile_attn_bwd(*part, *some, B, 8, F, T, d, mask, d ** -0.5, s)
+        ta.tile_attn_bwd(*part, *some, B, n, F, T, d, mask, d ** -0.5, s)
         for x, y in zip(whole, some):
-            assert torch.equal(x[:, h:h + 8].isnan(), y.isnan())
-            assert torch.equal(x[:, h:h + 8].nan_to_num(0.0), y.nan_to_num(0.0))
+            assert torch.equal(x[:, h:h + n].isnan(), y.isnan())
+            assert torch.equal(x[:, h:h + n].nan_to_num(0.0), y.nan_to_num(0.0))
